@@ -1969,10 +1969,12 @@ slg_status slg_components(slg_context *ctx, slg_graph *g, int32_t s, const int32
     int64_t *dev = nullptr;  // [0] roots, [1] error flags
     int32_t *parent = nullptr;
     SLG_HIP(ctx, sc.get(&dev, 2));
+    uint32_t *bits = nullptr;
     SLG_HIP(ctx, sc.get(&parent, m));
+    SLG_HIP(ctx, sc.get(&bits, edge_bits_words(m, num_edges)));
     SLG_HIP(ctx, launch_fill_i64(dev, 2, 0, st));
     SLG_HIP(ctx, launch_cc_init(g->inc.he_ptr, m, s, parent, st));
-    SLG_HIP(ctx, launch_cc_hook(row, col, num_edges, m, parent, reinterpret_cast<int *>(dev + 1), st));
+    SLG_HIP(ctx, launch_cc_hook(row, col, num_edges, m, parent, bits, reinterpret_cast<int *>(dev + 1), st));
     SLG_HIP(ctx, launch_cc_finish(m, parent, labels, reinterpret_cast<unsigned long long *>(dev), st));
     SLG_HIP(ctx, hipMemcpyAsync(ctx->pinned, dev, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, st));
     SLG_HIP(ctx, hipStreamSynchronize(st));
@@ -2003,9 +2005,13 @@ slg_status slg_components_noalloc(slg_context *ctx, slg_graph *g, int32_t s, con
     // two counters are cleared here and every parent is written by cc_init
     int64_t *dev = static_cast<int64_t *>(ctx->noalloc);  // [0] roots, [1] error flags
     int32_t *parent = reinterpret_cast<int32_t *>(dev + 2);
+    // the hook's bits are used up to 2^21 hyperedges: they fit behind the parents
+    uint32_t *bits = reinterpret_cast<uint32_t *>(parent + m);
+    if (m + edge_bits_words(m, num_edges) > kNoAllocRows)
+        return fail(ctx, SLG_ERR_INVALID_ARG, "internal error: the fixed scratch is too small");
     SLG_HIP(ctx, launch_fill_i64(dev, 2, 0, st));
     SLG_HIP(ctx, launch_cc_init(g->inc.he_ptr, m, s, parent, st));
-    SLG_HIP(ctx, launch_cc_hook(row, col, num_edges, m, parent, reinterpret_cast<int *>(dev + 1), st));
+    SLG_HIP(ctx, launch_cc_hook(row, col, num_edges, m, parent, bits, reinterpret_cast<int *>(dev + 1), st));
     SLG_HIP(ctx, launch_cc_finish(m, parent, labels, reinterpret_cast<unsigned long long *>(dev), st));
     SLG_HIP(ctx, hipMemcpyAsync(ctx->pinned, dev, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, st));
     SLG_HIP(ctx, hipStreamSynchronize(st));
@@ -2032,9 +2038,10 @@ slg_status slg_squeeze(slg_context *ctx, int64_t m, int32_t *row, int32_t *col, 
     SLG_HIP(ctx, sc.get(&pre, m + 1));
     SLG_HIP(ctx, sc.get(&part, scan_partials_size(m)));
     SLG_HIP(ctx, sc.get(&err, 1));
-    SLG_HIP(ctx, launch_fill_i32(flag, m, 0, st));
+    uint32_t *bits = nullptr;
+    SLG_HIP(ctx, sc.get(&bits, edge_bits_words(m, num_edges)));
     SLG_HIP(ctx, launch_fill_i64(err, 1, 0, st));
-    SLG_HIP(ctx, launch_mark_ends(row, col, num_edges, m, flag, reinterpret_cast<int *>(err), st));
+    SLG_HIP(ctx, launch_mark_ends(row, col, num_edges, m, flag, bits, reinterpret_cast<int *>(err), st));
     SLG_HIP(ctx, launch_exclusive_scan_i32(flag, m, pre, part, st));
     SLG_HIP(ctx, launch_squeeze_ids(m, flag, pre, new_id, st));
     SLG_HIP(ctx, hipMemcpyAsync(ctx->pinned, err, sizeof(int64_t), hipMemcpyDeviceToHost, st));

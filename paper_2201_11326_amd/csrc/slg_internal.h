@@ -275,14 +275,16 @@ hipError_t launch_gather_i64(const int64_t *src, const int64_t *idx, int64_t cou
 // the root of i, the smallest id of its component (or -1). count gets the
 // number of roots; err is set if a bounded loop ran out (never expected).
 hipError_t launch_cc_init(const int64_t *he_ptr, int64_t m, int32_t s, int32_t *label, hipStream_t st);
+// (bits: scratch of edge_bits_words(m, num_edges) words)
+int64_t edge_bits_words(int64_t m, int64_t num_edges);
 hipError_t launch_cc_hook(const int32_t *row, const int32_t *col, int64_t num_edges, int64_t m, int32_t *label,
-                          int *err, hipStream_t st);
+                          uint32_t *bits, int *err, hipStream_t st);
 hipError_t launch_cc_finish(int64_t m, const int32_t *label, int32_t *out, unsigned long long *count,
                             hipStream_t st);
-// ID squeezing: flag[i] = 1 for every end of an edge (ids outside [0, m):
-// err |= 4, also in the hook).
+// ID squeezing: flag[i] = 1 for every end of an edge, else 0 (ids outside
+// [0, m): err |= 4, also in the hook); bits as for the hook.
 hipError_t launch_mark_ends(const int32_t *row, const int32_t *col, int64_t num_edges, int64_t m, int32_t *flag,
-                            int *err, hipStream_t st);
+                            uint32_t *bits, int *err, hipStream_t st);
 // new_id[i] = pre[i] when flag[i], else -1 (pre: exclusive scan of flag).
 hipError_t launch_squeeze_ids(int64_t m, const int32_t *flag, const int64_t *pre, int32_t *new_id, hipStream_t st);
 // row[e] = new_id[row[e]], col[e] = new_id[col[e]].

@@ -104,3 +104,58 @@ def test_errors(ctx):
     with pytest.raises(slg.SlgError):
         ctx.squeeze(inc.m, bad)
     g.release()
+
+
+# Lists of 2^20 edges and more: sampled rounds first, then every edge against
+# bits in LDS (two sizes of it, by m) or against the labels (larger m).
+@pytest.mark.parametrize("m", [200_001, 327_681, 1_245_185])
+@pytest.mark.parametrize("shape", ["hubs", "blocks"])
+def test_long_edge_lists(ctx, m, shape):
+    import torch
+    from scipy.sparse import coo_matrix
+    from scipy.sparse.csgraph import connected_components
+    import paper_2201_11326_amd as slg
+    if shape == "hubs":  # one large component, many single hyperedges
+        _, row, col, w = hg.random_upper_edges(m, m, 1_300_000, exponent=0.5)
+    else:  # no large component: ids are joined inside blocks of 40 only
+        rng = np.random.default_rng(m)
+        a, b = rng.integers(0, m, 1_150_000), rng.integers(1, 40, 1_150_000)
+        row = a.astype(np.int32)
+        col = np.minimum(a // 40 * 40 + 39, np.minimum(a + b, m - 1)).astype(np.int32)
+        row, col = row[row < col], col[row < col]
+        row, col = np.resize(row, 1 << 20), np.resize(col, 1 << 20)  # repeats are allowed
+        w = np.ones(row.size, np.int32)
+    kept = np.ones(m, bool)
+    ends = np.zeros(m, bool)
+    ends[row] = ends[col] = True
+    kept[~ends] = np.arange(int((~ends).sum())) % 2 == 0  # some isolated ids lie outside E_1
+    size = kept.astype(np.int64)
+    he_ptr = np.concatenate([[0], np.cumsum(size)])
+    inc = hg.from_csr(m, m, he_ptr, np.nonzero(kept)[0].astype(np.int32))
+    g = ctx.register_incidence(inc)
+    dev = lambda x: torch.as_tensor(x).cuda()
+    lg = slg.LineGraph(1, None, dev(row), dev(col), dev(w), 0)
+    labels, count = ctx.components(g, 1, lg)
+    _, comp = connected_components(coo_matrix((np.ones(row.size), (row, col)), shape=(m, m)), directed=False)
+    first = np.full(comp.max() + 1, m, np.int64)
+    np.minimum.at(first, comp, np.arange(m))
+    ref = np.where(kept, first[comp], -1)
+    np.testing.assert_array_equal(labels.cpu().numpy(), ref)
+    assert count == np.unique(ref[ref >= 0]).size
+    fixed, count2 = ctx.components_noalloc(g, 1, lg)
+    assert count2 == count and torch.equal(fixed, labels)
+    new_id, num = ctx.squeeze(m, lg)
+    np.testing.assert_array_equal(new_id.cpu().numpy(), np.where(ends, np.cumsum(ends) - 1, -1))
+    assert num == ends.sum()
+    # ids outside [0, m), and an end outside E_s, anywhere in the list
+    for bad, what in ((m, "outside"), (-1, "outside"), (int(np.nonzero(~kept)[0][0]), "fewer than")):
+        for at in (0, 700_001, row.size - 1):
+            r = row.copy()
+            r[at] = bad
+            wrong = slg.LineGraph(1, None, dev(r), dev(col), dev(w), 0)
+            with pytest.raises(slg.SlgError, match=what):
+                ctx.components(g, 1, wrong)
+            if what == "outside":
+                with pytest.raises(slg.SlgError, match=what):
+                    ctx.squeeze(m, wrong)
+    g.release()
