@@ -835,14 +835,15 @@ def bench_large_skewed(args) -> int:
     roofline = {"bound": "hbm", "achieved": achieved, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                 "frac": achieved / PEAK_HBM_GBS if achieved else None, "traffic": measured_traffic("dense_kernel<false>", DENSE_TRAFFIC_PROFILE,
                                                                                      work["dense_two_paths"] / max(launches, 1)),
-                "kernel": "dense_kernel<false> (count_dense)", "launches": launches,
+                "kernel": "hub_count_kernel and dense_kernel<false> (count_dense)", "launches": launches,
                 "avg_launch_ms": count_ms / max(launches, 1),
                 "algorithmic_bytes_per_launch": dense_bytes / max(launches, 1),
                 "overhead_bytes_per_launch": {"dense_store_written": 4 * work["dense_stored"] / max(launches, 1)},
                 "sq_counters": measured_sq("dense_kernel<false>", DENSE_SQ_PROFILE),
-                "note": "window-major order serves most of the 2-paths' bytes from L2, so the algorithmic "
-                        "bytes can exceed what HBM delivers; `traffic` is the measured HBM bytes per launch",
-                "emit": {"kernel": "heavy_store_emit_kernel<4, true> (emit_dense)",
+                "note": "2-paths through the heaviest vertices are counted with matrix instructions and never read "
+                        "one by one, so the algorithmic bytes exceed what HBM delivers; `traffic` is the measured "
+                        "HBM bytes per launch",
+                "emit": {"kernel": "hub_emit_kernel and heavy_store_emit_kernel<4, true> (emit_dense)",
                          "launches": emit_launches, "ms": emit_ms,
                          "algorithmic_bytes": 12 * work["dense_edges"],
                          "achieved_gbs": 12 * work["dense_edges"] / (emit_ms / 1e3) / 1e9 if emit_ms > 0 else None}}

@@ -92,14 +92,20 @@ constexpr int kCntFill = kCntErr + 1;           // kNumLists: append cursors of 
 constexpr int kCntHeavyWork = kCntFill + kNumLists;  // 2-paths in heavy rows
 constexpr int kCntPieces = kCntHeavyWork + 1;     // large-row pieces of row planning
 constexpr int kCntDenseWork = kCntPieces + 1;     // 2-paths in dense rows
-constexpr int kCntTotal = kCntDenseWork + 1;
-static_assert(kCntTotal <= 32, "counter block");
+constexpr int kCntHubRows = kCntDenseWork + 1;    // hub rows (written with the dense 2-paths)
+constexpr int kCntTotal = kCntHubRows + 1;
+constexpr int kCntRoom = 32;
+static_assert(kCntTotal <= kCntRoom, "counter block");
+// With the hub tier its choice and histogram follow, cleared together.
+constexpr int kCntHubInfo = kCntRoom;
+static_assert(sizeof(HubInfo) % 8 == 0, "cleared as int64 words");
+constexpr int64_t kCntHubHist = kCntHubInfo + (int64_t)(sizeof(HubInfo) / 8);
 // Host staging slots for readbacks.
 constexpr int kHbSlots = kCntTotal;      // slot table size, then 2-paths, boundary entries
 constexpr int kHbEdges = 40;             // SLG_MAX_S edge totals
 constexpr int kHbHeavyEdges = kHbEdges + SLG_MAX_S;
 constexpr int kHbRange = kHbHeavyEdges + 7;  // a chunk's heavy list ranges (2 per list)
-static_assert(kHbSlots + 3 <= kHbEdges && kHbRange + 2 * kNumHeavyLists <= kPinnedSlots, "pinned staging layout");
+static_assert(kHbSlots + 3 <= kHbEdges && kHbRange + 2 * kNumHeavyLists + 2 <= kPinnedSlots, "pinned staging layout");
 // Device counters of a plan (int64 entries of `tickets`).
 constexpr int kTkCount = 0;       // kNumHeavyLists: slot tickets of the counting passes
 constexpr int kTkEmit = 3;        // kNumHeavyLists: slot tickets of the emit passes
@@ -306,6 +312,12 @@ struct PlanBufs {
     int64_t *kpre = nullptr;     // their exclusive scan,
     int32_t *cid = nullptr, *cid_row = nullptr, *vs_cid = nullptr;  // ranks, rows of ranks, lists in ranks
     uint16_t *vs_win = nullptr;  // the lists' ranks modulo the dense window
+    HubInfo *hub = nullptr;      // hub tier: the choice and its histogram,
+    int64_t *hub_hist = nullptr;
+    uint32_t *nib = nullptr;     // hub membership per rank (once per plan),
+    uint8_t *hub_flag = nullptr; // hub rows of the block: flags, prefix, list
+    int64_t *hub_pre = nullptr;
+    int32_t *hub_rows = nullptr;
 };
 
 struct slg_plan {
@@ -339,6 +351,9 @@ struct slg_plan {
     bool dense = false;            // rows may take the dense tier (E_s positions computed)
     int32_t dense_ratio = 0, dense_min = 0;
     int dense_grid = 0;
+    bool hubs = false;             // dense rows may take the hub tier (decided on the device)
+    int64_t hub_rows = 0;          // hub rows and slots of the block
+    int64_t hub_slots = 0;
     bool use_dstore = false;       // dense slots keep their survivors for the emit pass
     CountStore dstore{};
     int64_t dstore_cap = 0;        // entries of the dense store
@@ -600,7 +615,7 @@ hipError_t enqueue_rows(slg_plan *p, hipStream_t st) {
     const int64_t m = inc.num_hyperedges, n = inc.num_vertices, nnz = inc.nnz;
     PlanBufs &b = p->b;
     hipError_t e;
-    if ((e = launch_fill_i64(b.counters, 32, 0, st)) != hipSuccess) return e;
+    if ((e = launch_fill_i64(b.counters, p->hubs ? kCntHubHist + hub_hist_words() : kCntRoom, 0, st)) != hipSuccess) return e;
     if (p->prune) {
         StageTimer tm(ctx, kStPrune, st);
         if ((e = launch_keep_incidence(nnz, inc.v_idx, inc.he_ptr, m, p->s_min, p->pr.row_s, b.flag, st)) !=
@@ -617,12 +632,14 @@ hipError_t enqueue_rows(slg_plan *p, hipStream_t st) {
         if ((e = launch_exclusive_scan_u8(b.keep, m, b.kpre, b.part_m, st)) != hipSuccess) return e;
         if ((e = launch_cid(m, b.keep, b.kpre, b.cid, b.cid_row, st)) != hipSuccess) return e;
         if ((e = launch_vs_cid(n, m, nnz, p->pr.vs_ptr, p->pr.vs_idx, b.cid, b.vs_cid, b.vs_win, st)) != hipSuccess) return e;
+        if (p->hubs && (e = launch_hub_select(n, p->pr.vs_ptr, b.kpre + m, b.hub, b.hub_hist, st)) != hipSuccess)
+            return e;
     }
     {
         StageTimer tm(ctx, kStRowPlan, st);
         if ((e = launch_row_plan(p->pr, p->s_min, p->light_max, p->slot_work, p->plan_lo,
                                  p->plan_hi < 0 ? m : p->plan_hi, p->dense ? p->dense_ratio : 0,
-                                 p->dense_min, b.tail_beg, b.work, b.jmax, b.nslots, b.rclass, b.bsize,
+                                 p->dense_min, p->hubs ? b.hub : nullptr, b.tail_beg, b.work, b.jmax, b.nslots, b.rclass, b.bsize,
                                  reinterpret_cast<unsigned long long *>(b.counters + kCntClass),
                                  reinterpret_cast<int *>(b.counters + kCntErr),
                                  reinterpret_cast<unsigned long long *>(b.counters + kCntHeavyWork),
@@ -690,6 +707,11 @@ struct AuxFork {
     }
     ~AuxFork() { (void)join(); }
 };
+
+// Hub rows [lo, hi) of the block's list.
+HubRows hub_range(const slg_plan *p, int64_t lo, int64_t hi) {
+    return {p->b.hub_rows, lo, hi, p->kept_rows, p->b.nslots, p->slot_base, p->b.hub, p->b.nib};
+}
 
 hipError_t enqueue_slots_count(slg_plan *p, hipStream_t st) {
     slg_context *ctx = p->ctx;
@@ -789,6 +811,18 @@ hipError_t enqueue_slots_count(slg_plan *p, hipStream_t st) {
                               p->tickets + kTkDenseCursor, p->dstore_cap, st)) != hipSuccess)
             return e;
     }
+    if (p->hub_rows > 0) {
+        {
+            StageTimer tm(ctx, kStSlots, st);
+            if ((e = launch_hub_rows(m, b.rclass, b.hub_flag, b.hub_pre, b.part_m, p->hub_rows, b.hub_rows, st)) !=
+                hipSuccess)
+                return e;
+        }
+        StageTimer tm(ctx, kStCountDense, st);
+        if ((e = launch_hub(false, hub_range(p, 0, p->hub_rows), p->pr, p->prm, p->S, p->slot_cnt, nullptr, st)) !=
+            hipSuccess)
+            return e;
+    }
     StageTimer tm(ctx, kStCountScans, st);
     for (int k = 0; k < p->prm.k; ++k)
         if ((e = launch_exclusive_scan_i64(p->slot_cnt + (size_t)k * p->S, p->S,
@@ -855,12 +889,14 @@ slg_status plan_rows(slg_plan *p) {
         phase1.add(&b.vs_cid, nnz + kDensePad);
         phase1.add(&b.vs_win, nnz + kDensePad);  // the dense walk may load (not count) past the end
     }
+    // smaller graphs never have the 2-paths the hub tier asks for
+    p->hubs = p->dense && nnz >= (1 << 17) && m >= kDenseWindow && p->s_min <= kHubMaxS;
     if (p->blocks) {
         phase1.add(&b.nslots_all, m);
         phase1.add(&b.rclass_all, m);
         phase1.add(&b.bsize_all, m);
     }
-    phase1.add(&b.counters, 32);
+    phase1.add(&b.counters, p->hubs ? kCntHubHist + hub_hist_words() : kCntRoom);
     phase1.add(&b.pieces, 3 * plan_pieces_cap(nnz));
     phase1.add(&b.part_m, scan_partials_size(m));
     phase1.add(&p->slot_base, m + 1);
@@ -875,6 +911,10 @@ slg_status plan_rows(slg_plan *p) {
     } else {
         pr.vs_ptr = inc.v_ptr;
         pr.vs_idx = inc.v_idx;
+    }
+    if (p->hubs) {
+        b.hub = reinterpret_cast<HubInfo *>(b.counters + kCntHubInfo);
+        b.hub_hist = b.counters + kCntHubHist;
     }
     pr.tail_beg = b.tail_beg;
     pr.cid = b.cid;
@@ -904,6 +944,8 @@ slg_status plan_rows(slg_plan *p) {
     p->nbounds = hb[kHbSlots + 2];
     p->heavy_two_paths = hb[kCntHeavyWork];
     p->dense_two_paths = hb[kCntDenseWork];
+    p->hub_rows = hb[kCntHubRows];
+    p->hub_slots = p->list_count[kNumLists - 1];
     p->row_lo = 0;
     p->row_hi = m;
     return SLG_OK;
@@ -924,7 +966,7 @@ slg_status plan_block(slg_plan *p, int64_t r0, int64_t r1) {
     sc.release();
     if (r0 > 0 || r1 < m) {
         if (!p->blocks) return fail(ctx, SLG_ERR_INVALID_ARG, "internal error: a row block of a whole plan");
-        BUILD_HIP(launch_fill_i64(b.counters, 32, 0, st));
+        BUILD_HIP(launch_fill_i64(b.counters, kCntRoom, 0, st));
         BUILD_HIP(launch_block_mask(m, r0, r1, b.nslots_all, b.rclass_all, b.bsize_all, b.work, b.nslots, b.rclass,
                                     b.bsize, reinterpret_cast<unsigned long long *>(b.counters + kCntClass),
                                     reinterpret_cast<unsigned long long *>(b.counters + kCntHeavyWork),
@@ -943,6 +985,8 @@ slg_status plan_block(slg_plan *p, int64_t r0, int64_t r1) {
         p->nbounds = hb[kHbSlots + 2];
         p->heavy_two_paths = hb[kCntHeavyWork];
         p->dense_two_paths = hb[kCntDenseWork];
+        p->hub_rows = hb[kCntHubRows];
+        p->hub_slots = p->list_count[kNumLists - 1];
     } else if (p->blocks && (p->row_lo != 0 || p->row_hi != m)) {
         return fail(ctx, SLG_ERR_INVALID_ARG, "internal error: all rows after a row block");
     }
@@ -952,7 +996,13 @@ slg_status plan_block(slg_plan *p, int64_t r0, int64_t r1) {
     if (p->nbounds >= (int64_t(1) << 40)) return fail(ctx, SLG_ERR_OVERFLOW, "boundary table too large");
 
     const int K = p->prm.k;
-    AllocList phase2;
+    AllocList phase2, hub_once;
+    if (p->hub_rows > 0) {
+        phase2.add(&b.hub_flag, m);
+        phase2.add(&b.hub_pre, m + 1);
+        phase2.add(&b.hub_rows, p->hub_rows);
+        if (!b.nib) hub_once.add(&b.nib, hub_nib_words(p->kept_rows));  // for the plan's life
+    }
     phase2.add(&b.slot_row, p->S);
     phase2.add(&p->bounds, p->nbounds);
     phase2.add(&p->tickets, kTkTotal);
@@ -1007,10 +1057,16 @@ slg_status plan_block(slg_plan *p, int64_t r0, int64_t r1) {
         }
     }
     if (p->reserve) {
-        if (!(*p->reserve)(phase2.bytes)) return fail(ctx, SLG_ERR_OUT_OF_MEMORY, "device-memory budget refused");
-        p->reserved += phase2.bytes;
+        if (!(*p->reserve)(phase2.bytes + hub_once.bytes))
+            return fail(ctx, SLG_ERR_OUT_OF_MEMORY, "device-memory budget refused");
+        p->reserved += phase2.bytes + hub_once.bytes;
     }
     for (const auto &a : phase2.items) BUILD_HIP(sc.get(a.first, a.second));
+    for (const auto &a : hub_once.items) BUILD_HIP(p->scratch.get(a.first, a.second));
+    if (!hub_once.items.empty()) {
+        StageTimer tm(ctx, kStSlots, st);
+        BUILD_HIP(launch_hub_bits(p->pr.n, b.hub, p->pr.vs_ptr, b.vs_cid, p->kept_rows, b.nib, st));
+    }
     if (p->dstore_fixed && p->use_dstore) p->dstore.ent = p->dstore_fixed;
     p->slots.count = p->S;
     p->slots.row = b.slot_row;
@@ -1023,6 +1079,9 @@ slg_status plan_block(slg_plan *p, int64_t r0, int64_t r1) {
                                      p->tickets + kTkHeavyEdges, st));
     BUILD_HIP(launch_heavy_edges(p->heavy[2], p->list_count[kLightClasses + 2], p->slot_cnt, p->S, K,
                                  p->tickets + kTkDenseEdges, st));
+    if (p->hub_rows > 0)
+        BUILD_HIP(launch_hub_edges(hub_range(p, 0, p->hub_rows), p->S, p->slot_off, K, p->tickets + kTkDenseEdges,
+                                   st));
     if (p->use_store)
         BUILD_HIP(launch_sum_i32(p->store.n, p->list_count[kLightClasses], p->tickets + kTkStored, st));
     BUILD_HIP(hipMemcpyAsync(hb + kHbHeavyEdges, p->tickets + kTkHeavyEdges, 6 * sizeof(int64_t),
@@ -1046,7 +1105,7 @@ slg_status plan_block(slg_plan *p, int64_t r0, int64_t r1) {
     for (int k = 0; k < K; ++k) wk[kWkEdges] += p->num_edges[k];
     wk[kWkHeavyEdges] += p->heavy_edges;
     wk[kWkDenseEdges] += p->dense_edges;
-    wk[kWkDenseSlots] += p->list_count[kLightClasses + 2];
+    wk[kWkDenseSlots] += p->list_count[kLightClasses + 2] + p->hub_slots;
     wk[kWkDenseStored] += p->dense_kept;
     wk[kWkDenseRewalk] += (p->list_count[kLightClasses + 2] > 0 && p->dense_stored > p->dense_kept) ? 1 : 0;
     return SLG_OK;
@@ -1124,7 +1183,7 @@ namespace {
 // first entry is global edge offset base[k]; row_ptr[k] gets r1 - r0 + 1
 // entries relative to base[k].
 // lists (optional, host): the chunk's part [lists[2h], lists[2h+1]) of
-// heavy list h, known beforehand; else found on the device and read back.
+// heavy list h (and, last, of the hub rows), known beforehand; else found on the device and read back.
 slg_status emit_range(slg_plan *p, int64_t r0, int64_t r1, int64_t s0, int64_t s1, const int64_t *base,
                       int64_t *const *row_ptr, int32_t *const *row, int32_t *const *col, int32_t *const *w,
                       hipStream_t st, const int64_t *lists = nullptr) {
@@ -1156,7 +1215,10 @@ slg_status emit_range(slg_plan *p, int64_t r0, int64_t r1, int64_t s0, int64_t s
     // in slot order), found on the device and read back
     int64_t lo[kNumHeavyLists] = {}, hi[kNumHeavyLists];
     for (int h = 0; h < kNumHeavyLists; ++h) hi[h] = p->list_count[kLightClasses + h];
+    int64_t hub_lo = 0, hub_hi = p->hub_rows;  // and of the hub rows
     if (lists) {
+        hub_lo = lists[2 * kNumHeavyLists];
+        hub_hi = lists[2 * kNumHeavyLists + 1];
         for (int h = 0; h < kNumHeavyLists; ++h) {
             lo[h] = lists[2 * h];
             hi[h] = lists[2 * h + 1];
@@ -1169,7 +1231,16 @@ slg_status emit_range(slg_plan *p, int64_t r0, int64_t r1, int64_t s0, int64_t s
             SLG_HIP(ctx, hipMemcpyAsync(hb + 2 * h, p->tickets + kTkRange + 2 * h, 2 * sizeof(int64_t),
                                         hipMemcpyDeviceToHost, st));
         }
+        if (p->hub_rows > 0) {
+            int64_t *hr = hb + 2 * kNumHeavyLists;
+            SLG_HIP(ctx, hipMemcpyAsync(hr, p->b.hub_pre + r0, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+            SLG_HIP(ctx, hipMemcpyAsync(hr + 1, p->b.hub_pre + r1, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+        }
         SLG_HIP(ctx, hipStreamSynchronize(st));
+        if (p->hub_rows > 0) {
+            hub_lo = hb[2 * kNumHeavyLists];
+            hub_hi = hb[2 * kNumHeavyLists + 1];
+        }
         for (int h = 0; h < kNumHeavyLists; ++h)
             if (hi[h] > 0) {
                 lo[h] = hb[2 * h];
@@ -1200,6 +1271,10 @@ slg_status emit_range(slg_plan *p, int64_t r0, int64_t r1, int64_t s0, int64_t s
             SLG_HIP(ctx, launch_dense(true, p->heavy[2] + lo[2], cnt, nullptr, p->S, p->bounds, p->pr, prm, nullptr,
                                       p->slot_off, p->tickets + kTkEmit + 2, p->dense_grid,
                                       p->use_dstore ? &part : nullptr, nullptr, 0, st));
+    }
+    if (hub_hi > hub_lo) {
+        StageTimer tm(ctx, kStEmitDense, st);
+        SLG_HIP(ctx, launch_hub(true, hub_range(p, hub_lo, hub_hi), p->pr, prm, p->S, nullptr, p->slot_off, st));
     }
     {
         StageTimer tm(ctx, kStRowPtr, st);
@@ -1365,7 +1440,7 @@ slg_status stream_rows(slg_context *ctx, slg_graph *g, const int32_t *s, int32_t
             double r = (double)nsl[b1] * (24.0 + 16.0 * K) + 4.0 * (double)bsz[b1], d = 0;
             if (c == kHeavy || c == kHeavyWide) r += 4.0 * (double)work[b1];
             else if (c == kDense) d = per_dense * (double)work[b1];
-            else if (c != kNone) r += 6.0 * (double)work[b1];
+            else if (c != kNone && c != kDenseHub) r += 6.0 * (double)work[b1];
             if (b1 > b0 && (bytes + r > 0.25 * (double)budget || (dense_room > 0 && entries + d > dense_room)))
                 break;
             bytes += r;
@@ -1409,18 +1484,22 @@ slg_status stream_rows(slg_context *ctx, slg_graph *g, const int32_t *s, int32_t
         STREAM_HIP(p->scratch2.get(&doffs, nc * K));
         STREAM_HIP(hipMemcpyAsync(dcuts, cuts.data(), nc * sizeof(int64_t), hipMemcpyHostToDevice, st));
         STREAM_HIP(launch_gather_offsets(dcuts, nc, p->slot_base, p->slot_off, p->S, K, doffs, st));
-        std::vector<int64_t> offs(nc * K), sb(nc), parts(kNumHeavyLists * nc);
+        std::vector<int64_t> offs(nc * K), sb(nc), parts((kNumHeavyLists + 1) * nc);
         // first slot of every cut row, then where each heavy list reaches it
         int64_t *dsb, *dparts;
         STREAM_HIP(p->scratch2.get(&dsb, nc));
-        STREAM_HIP(p->scratch2.get(&dparts, kNumHeavyLists * nc));
+        STREAM_HIP(p->scratch2.get(&dparts, (kNumHeavyLists + 1) * nc));
         STREAM_HIP(launch_gather_i64(p->slot_base, dcuts, nc, dsb, st));
         for (int h = 0; h < kNumHeavyLists; ++h)
             STREAM_HIP(launch_list_cuts(p->heavy[h], p->list_count[kLightClasses + h], dsb, nc, dparts + h * nc, st));
+        if (p->hub_rows > 0)  // hub rows before every cut row
+            STREAM_HIP(launch_gather_i64(p->b.hub_pre, dcuts, nc, dparts + kNumHeavyLists * nc, st));
+        else
+            STREAM_HIP(launch_fill_i64(dparts + kNumHeavyLists * nc, nc, 0, st));
         STREAM_HIP(hipMemcpyAsync(offs.data(), doffs, nc * K * sizeof(int64_t), hipMemcpyDeviceToHost, st));
         STREAM_HIP(hipMemcpyAsync(sb.data(), dsb, nc * sizeof(int64_t), hipMemcpyDeviceToHost, st));
-        STREAM_HIP(hipMemcpyAsync(parts.data(), dparts, kNumHeavyLists * nc * sizeof(int64_t), hipMemcpyDeviceToHost,
-                                  st));
+        STREAM_HIP(hipMemcpyAsync(parts.data(), dparts, (kNumHeavyLists + 1) * nc * sizeof(int64_t),
+                                  hipMemcpyDeviceToHost, st));
         STREAM_HIP(hipStreamSynchronize(st));
         // two buffer sets for the largest chunk of every threshold so far:
         // they grow when a block needs more, and are kept otherwise
@@ -1457,8 +1536,8 @@ slg_status stream_rows(slg_context *ctx, slg_graph *g, const int32_t *s, int32_t
                 rjk[k] = rj[t][k];
                 rwk[k] = rw[t][k];
             }
-            int64_t lists[2 * kNumHeavyLists];
-            for (int h = 0; h < kNumHeavyLists; ++h) {
+            int64_t lists[2 * kNumHeavyLists + 2];
+            for (int h = 0; h <= kNumHeavyLists; ++h) {
                 lists[2 * h] = parts[h * nc + c];
                 lists[2 * h + 1] = parts[h * nc + c + 1];
             }
@@ -1531,7 +1610,7 @@ slg_status slg_plan_stats(const slg_plan *p, int64_t *out, int32_t cap, int32_t 
     vals[12] = p->nbounds;
     vals[13] = p->heavy_edges;
     vals[14] = p->stored_ranks;
-    vals[15] = p->list_count[kLightClasses + 2];
+    vals[15] = p->list_count[kLightClasses + 2] + p->hub_slots;
     vals[16] = p->dense_two_paths;
     vals[17] = p->dense_edges;
     vals[18] = p->dense_kept;

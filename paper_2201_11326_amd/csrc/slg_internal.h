@@ -29,6 +29,14 @@ constexpr int kDenseThreads = 512;            // workgroup of the dense tier (2 
 constexpr int kDenseRatio = 4;                // default: 2-paths per 8 candidate partners to go dense
 constexpr int kDenseMinRange = 8192;          // default: fewest candidate partners to go dense
 constexpr int kDensePad = 1024;  // entries past the end of the E_s-position lists the dense walk may load
+// Hub tier (slg_hub.hip): dense rows whose 2-paths run mostly through at most
+// kHubs vertices count with matrix instructions, kHubRows rows at a time.
+constexpr int kHubs = 120;            // and eight values for the threshold: 128 in a matrix operand
+constexpr int kHubMaxS = 44;          // largest s_min those eight fp4 values can take off
+constexpr int kHubMaxMembers = 255;   // overlaps of hub rows fit 8 bits
+constexpr int kHubRows = 32;
+constexpr double kHubMinPaths = double(1 << 28);  // fewest 2-paths of the graph for which its setup pays
+constexpr double kHubMaxRest = 0.125;  // most 2-paths outside the hubs per pair of kept rows
 constexpr long long kDenseChunk = 1 << 16;  // dense-store entries a workgroup takes at a time
 
 // Row classes written by the planning kernel.
@@ -37,9 +45,10 @@ enum RowClass : uint8_t {
     kLight0 = 1,
     kHeavy = kLight0 + kLightClasses,  // bitmap-rank tier, u16 counters
     kHeavyWide = kHeavy + 1,           // bitmap-rank tier, u32 counters
-    kDense = kHeavyWide + 1            // direct-counter tier over E_s windows
+    kDense = kHeavyWide + 1,           // direct-counter tier over E_s windows
+    kDenseHub = kDense + 1             // the same windows, counted by the hub tier
 };
-constexpr int kNumLists = kLightClasses + 3;  // light classes + heavy + heavy-wide + dense slots
+constexpr int kNumLists = kLightClasses + 4;  // light classes + heavy + heavy-wide + dense + hub slots
 constexpr int kNumHeavyLists = 3;             // heavy, heavy-wide, dense descriptor lists
 
 // Per-call parameters, passed by value and staged in LDS by each kernel so
@@ -77,6 +86,27 @@ struct Pruned {
     const int32_t *cid_row;
     const int32_t *vs_cid;
     const uint16_t *vs_win;
+};
+
+// The hub tier's choice, made on the device by the rows phase: the vertices of
+// degree at least min_degree (at most kHubs of them) are hubs; `use` when the
+// plan's dense rows take the tier.
+struct HubInfo {
+    int32_t min_degree, use, count, done;
+    unsigned long long all_paths, hub_paths;  // 2-paths of the pruned graph, and those through hubs
+    int32_t vertex[kHubs];
+};
+
+// The hub rows [lo, hi) of a launch (ascending ids in `rows`) and what every
+// launch reads: nib = kHubs fp4 values per rank of E_s (1.0: the hub lies in
+// the rank's row), zero up to the end of the last window.
+struct HubRows {
+    const int32_t *rows;
+    int64_t lo, hi, kept;
+    const int32_t *nslots;
+    const int64_t *slot_base;
+    const HubInfo *info;
+    const uint32_t *nib;
 };
 
 // Slot table: a slot is (row i, hyperedge-id range) with its own output
@@ -156,12 +186,13 @@ hipError_t launch_vs_cid(int64_t n, int64_t m, int64_t nnz, const int64_t *vs_pt
 
 // K1/K2: per kept row, tail offsets, 2-path work, last partner, slot count.
 // dense_ratio = 0 keeps every row off the dense tier (then g.cid may be
-// null); dense_work gets the 2-paths of dense rows.
+// null); with hub->use (hub may be null) dense rows are hub rows. dense_work
+// gets the 2-paths of dense and hub rows, dense_work[1] the hub rows.
 // Rows outside [row_lo, row_hi) are planned as pruned rows (no work, no
 // slots); their member tails are not located.
 hipError_t launch_row_plan(const Pruned &g, int32_t s_min, int32_t light_max, int64_t slot_work, int64_t row_lo,
-                           int64_t row_hi, int32_t dense_ratio, int32_t dense_min, int32_t *tail_beg, int64_t *work,
-                           int32_t *jmax, int32_t *nslots, uint8_t *rclass, int64_t *bsize,
+                           int64_t row_hi, int32_t dense_ratio, int32_t dense_min, const HubInfo *hub, int32_t *tail_beg,
+                           int64_t *work, int32_t *jmax, int32_t *nslots, uint8_t *rclass, int64_t *bsize,
                            unsigned long long *class_count, int *err, unsigned long long *heavy_work,
                            unsigned long long *dense_work, int64_t *pieces, unsigned long long *num_pieces,
                            hipStream_t st);
@@ -229,6 +260,24 @@ hipError_t launch_dense(bool emit, const HeavyDesc *desc, int64_t count, const i
                         const Pruned &g, const EmitParams &ep, int64_t *slot_cnt, const int64_t *slot_off,
                         int64_t *ticket, int resident, const CountStore *store, int64_t *store_cursor,
                         int64_t store_cap, hipStream_t st);
+// Hub tier. launch_hub_select: chooses the hubs of the pruned vertex lists
+// (kept: the number of kept rows, on the device; info and hist,
+// hub_hist_words(), zeroed).
+// launch_hub_bits: nib, hub_nib_words(kept) words, from the hubs' lists.
+// launch_hub_rows: pre[i] = hub rows before i, rows = the hub rows. launch_hub:
+// the counting pass (slot_cnt) or the emit pass of rows [lo, hi).
+int64_t hub_hist_words();
+hipError_t launch_hub_select(int64_t n, const int64_t *vs_ptr, const int64_t *kept, HubInfo *info, int64_t *hist,
+                             hipStream_t st);
+int64_t hub_nib_words(int64_t kept);
+hipError_t launch_hub_bits(int64_t n, HubInfo *info, const int64_t *vs_ptr, const int32_t *vs_cid, int64_t kept,
+                           uint32_t *nib, hipStream_t st);
+hipError_t launch_hub_rows(int64_t m, const uint8_t *rclass, uint8_t *flag, int64_t *pre, int64_t *partials,
+                           int64_t cap, int32_t *rows, hipStream_t st);
+hipError_t launch_hub_edges(const HubRows &h, int64_t slots, const int64_t *slot_off, int32_t K, int64_t *out,
+                            hipStream_t st);
+hipError_t launch_hub(bool emit, const HubRows &h, const Pruned &g, const EmitParams &ep, int64_t slots,
+                      int64_t *slot_cnt, const int64_t *slot_off, hipStream_t st);
 // key[t] = the E_s window of dense slot t (its ja >> kDenseBits), id[t] = t.
 hipError_t launch_dense_keys(const HeavyDesc *desc, int64_t count, int32_t *key, int32_t *id, hipStream_t st);
 // Workgroups of the dense kernel that fit on the device at once.

@@ -32,132 +32,11 @@
 
 #include <type_traits>
 
+#include "slg_device.h"
 #include "slg_internal.h"
 
 namespace slg {
 namespace {
-
-// ---------------------------------------------------------------------------
-// wavefront / workgroup primitives
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ int lane_id() { return __lane_id(); }
-
-// Pointers that reach a kernel through LDS or a struct in memory lose their
-// address space; naming it keeps their accesses global_* (flat accesses also
-// count against the LDS wait counter, so every LDS wait would wait for them).
-template <typename T>
-__device__ __forceinline__ __attribute__((address_space(1))) T *as_global(T *p) {
-    return (__attribute__((address_space(1))) T *)p;
-}
-
-// Wavefront-uniform values moved to scalar registers.
-__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
-__device__ __forceinline__ long long uniform(long long x) {
-    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(x & 0xFFFFFFFFll));
-    const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)((unsigned long long)x >> 32));
-    return (long long)(((unsigned long long)hi << 32) | lo);
-}
-template <typename T>
-__device__ __forceinline__ T *uniform(T *p) {
-    return reinterpret_cast<T *>(uniform((long long)reinterpret_cast<uintptr_t>(p)));
-}
-
-__device__ __forceinline__ int bits_below(unsigned long long mask) {
-    return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
-                                     __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
-}
-
-// LDS writes of this wavefront become visible to its other lanes.
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-template <typename T>
-__device__ __forceinline__ T wave_sum(T x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-    return x;
-}
-
-__device__ __forceinline__ int wave_max(int x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x = max(x, __shfl_xor(x, o));
-    return x;
-}
-
-template <typename T>
-__device__ __forceinline__ T wave_incl_scan(T x) {
-    const int lane = lane_id();
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        T y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-    }
-    return x;
-}
-
-// Exclusive scan over a workgroup of NT threads; `wsum` holds NT/64 entries.
-template <int NT, typename T>
-__device__ __forceinline__ T block_excl_scan(T x, T *wsum, T &total) {
-    const int lane = lane_id(), wave = threadIdx.x >> 6;
-    T incl = wave_incl_scan(x);
-    if (lane == 63) wsum[wave] = incl;
-    __syncthreads();
-    T pre = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < NT / 64; ++w) {
-        T t = wsum[w];
-        pre += (w < wave) ? t : T(0);
-        tot += t;
-    }
-    total = tot;
-    __syncthreads();
-    return pre + incl - x;
-}
-
-// As block_excl_scan, without the trailing barrier: the caller guarantees
-// a workgroup barrier before `wsum` is written again.
-template <int NT, typename T>
-__device__ __forceinline__ T block_excl_scan_open(T x, T *wsum, T &total) {
-    const int lane = lane_id(), wave = threadIdx.x >> 6;
-    T incl = wave_incl_scan(x);
-    if (lane == 63) wsum[wave] = incl;
-    __syncthreads();
-    T pre = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < NT / 64; ++w) {
-        T t = wsum[w];
-        pre += (w < wave) ? t : T(0);
-        tot += t;
-    }
-    total = tot;
-    return pre + incl - x;
-}
-
-// Copy the by-value parameter block into LDS, one dword per thread (the
-// caller follows with a workgroup barrier).
-__device__ __forceinline__ void stage_params(EmitParams *dst, const EmitParams &src) {
-    constexpr int kWords = (int)(sizeof(EmitParams) / 4);
-    static_assert(sizeof(EmitParams) % 4 == 0, "EmitParams is dword-sized");
-    const int32_t *from = reinterpret_cast<const int32_t *>(&src);
-    int32_t *to = reinterpret_cast<int32_t *>(dst);
-    for (int x = threadIdx.x; x < kWords; x += blockDim.x) to[x] = from[x];
-}
-
-// First position in a[lo, hi) holding a value >= key (a sorted ascending).
-__device__ __forceinline__ int lower_bound_i32(const int32_t *__restrict__ a, int lo, int hi,
-                                               int key) {
-    while (lo < hi) {
-        int mid = (lo + hi) >> 1;
-        if (a[mid] < key)
-            lo = mid + 1;
-        else
-            hi = mid;
-    }
-    return lo;
-}
 
 // ---------------------------------------------------------------------------
 // device-wide exclusive scan (int64 output, out[n] = total)
@@ -344,7 +223,8 @@ struct RowPlanOut {
     int64_t *bsize;
     int32_t dense_ratio;  // the dense tier's rule (0: off)
     int32_t dense_min;
-    unsigned long long *dense_work;
+    const HubInfo *hub;  // the hub tier's choice, or null
+    unsigned long long *dense_work;  // 2-paths of dense and hub rows, then the number of hub rows
 };
 
 // One member of row i: its tail in v's list; returns false when the
@@ -370,7 +250,9 @@ __device__ __forceinline__ bool plan_member(const Pruned &g, int64_t i, int64_t 
     return found;
 }
 
-// Tier, slot count and boundary-table size of row i from its totals. A
+// Tier, slot count and boundary-table size of row i from its totals. hwork
+// (LDS): the workgroup's 2-paths of heavy rows, of dense and hub rows, and
+// its hub rows. A
 // heavy row goes to the dense tier when its candidate partners (the kept
 // rows in (i, jm]) number at least dense_min and it has at least
 // dense_ratio 2-paths per eight candidates: its slots are then the aligned
@@ -393,7 +275,7 @@ __device__ __forceinline__ void plan_finish(const Pruned &g, int64_t i, int64_t 
             cls = kLight0 + light_class(w);
             ns = 1;
         } else if (ci >= 0 && cj > ci && crange >= o.dense_min && 8 * w >= (int64_t)o.dense_ratio * crange) {
-            cls = kDense;
+            cls = o.hub && o.hub->use && p1 - p0 <= kHubMaxMembers ? kDenseHub : kDense;
             ns = (cj >> kDenseBits) - ((ci + 1) >> kDenseBits) + 1;
         } else {
             cls = (p1 - p0 >= kWideMembers) ? kHeavyWide : kHeavy;
@@ -408,10 +290,11 @@ __device__ __forceinline__ void plan_finish(const Pruned &g, int64_t i, int64_t 
     o.jmax[i] = jm;
     o.nslots[i] = (int32_t)ns;
     o.rclass[i] = (uint8_t)cls;
-    o.bsize[i] = cls >= kHeavy ? (ns + 1) * (p1 - p0) : 0;
+    o.bsize[i] = cls >= kHeavy && cls != kDenseHub ? (ns + 1) * (p1 - p0) : 0;  // hub rows keep no boundaries
     if (cls != kNone) atomicAdd(&ccount[cls - 1], (unsigned long long)ns);
     if (cls == kHeavy || cls == kHeavyWide) atomicAdd(hwork, (unsigned long long)w);
-    if (cls == kDense) atomicAdd(o.dense_work, (unsigned long long)w);
+    if (cls == kDense || cls == kDenseHub) atomicAdd(hwork + 1, (unsigned long long)w);
+    if (cls == kDenseHub) atomicAdd(hwork + 2, 1ull);
 }
 
 // Small and middle rows, and the piece list of the large ones: a large row
@@ -426,9 +309,9 @@ __global__ __launch_bounds__(256) void row_plan_kernel(Pruned g, int32_t s_min, 
                                                        int64_t *__restrict__ pieces, int64_t pieces_cap,
                                                        unsigned long long *__restrict__ num_pieces) {
     __shared__ unsigned long long ccount[kNumLists];
-    __shared__ unsigned long long hwork;
+    __shared__ unsigned long long hwork[3];
     if (threadIdx.x < kNumLists) ccount[threadIdx.x] = 0;
-    if (threadIdx.x == 0) hwork = 0;
+    if (threadIdx.x < 3) hwork[threadIdx.x] = 0;
     __syncthreads();
     const int lane = lane_id();
     const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x / 64);
@@ -439,7 +322,7 @@ __global__ __launch_bounds__(256) void row_plan_kernel(Pruned g, int32_t s_min, 
         if (i < g.m) {
             const int64_t p0 = g.he_ptr[i], p1 = g.he_ptr[i + 1];
             if (p0 < 0 || p1 > g.nnz || p1 < p0) {  // malformed pointers
-                plan_finish(g, i, p0, p1, 0, -1, true, light_max, slot_work, o, ccount, &hwork, err);
+                plan_finish(g, i, p0, p1, 0, -1, true, light_max, slot_work, o, ccount, hwork, err);
             } else {
                 const int64_t size = p1 - p0;
                 // rows outside [row_lo, row_hi) are planned as pruned ones
@@ -454,7 +337,7 @@ __global__ __launch_bounds__(256) void row_plan_kernel(Pruned g, int32_t s_min, 
                     bool rbad = false;
                     if (kept)
                         for (int64_t p = p0; p < p1; ++p) rbad |= !plan_member(g, i, p, o.tail_beg, w, jm);
-                    plan_finish(g, i, p0, p1, w, jm, rbad, light_max, slot_work, o, ccount, &hwork, err);
+                    plan_finish(g, i, p0, p1, w, jm, rbad, light_max, slot_work, o, ccount, hwork, err);
                 }
             }
         }
@@ -473,7 +356,7 @@ __global__ __launch_bounds__(256) void row_plan_kernel(Pruned g, int32_t s_min, 
             w = wave_sum(w);
             jm = wave_max(jm);
             rbad = wave_max(rbad);
-            if (lane == 0) plan_finish(g, r, q0, q1, w, jm, rbad != 0, light_max, slot_work, o, ccount, &hwork, err);
+            if (lane == 0) plan_finish(g, r, q0, q1, w, jm, rbad != 0, light_max, slot_work, o, ccount, hwork, err);
         }
         // one reservation per wavefront for the pieces of its large rows
         const unsigned long long incl = wave_incl_scan(np);
@@ -494,7 +377,8 @@ __global__ __launch_bounds__(256) void row_plan_kernel(Pruned g, int32_t s_min, 
     __syncthreads();
     if (threadIdx.x < kNumLists && ccount[threadIdx.x])
         atomicAdd(&class_count[threadIdx.x], ccount[threadIdx.x]);
-    if (threadIdx.x == 0 && hwork) atomicAdd(heavy_work, hwork);
+    if (threadIdx.x == 0 && hwork[0]) atomicAdd(heavy_work, hwork[0]);
+    if (threadIdx.x < 2 && hwork[1 + threadIdx.x]) atomicAdd(o.dense_work + threadIdx.x, hwork[1 + threadIdx.x]);
 }
 
 // One wavefront per piece of a large row: the piece's tails and its largest
@@ -539,9 +423,9 @@ __global__ __launch_bounds__(256) void row_piece_finish_kernel(Pruned g, int32_t
                                                                const int64_t *__restrict__ piece_w,
                                                                const int32_t *__restrict__ piece_jm) {
     __shared__ unsigned long long ccount[kNumLists];
-    __shared__ unsigned long long hwork;
+    __shared__ unsigned long long hwork[3];
     if (threadIdx.x < kNumLists) ccount[threadIdx.x] = 0;
-    if (threadIdx.x == 0) hwork = 0;
+    if (threadIdx.x < 3) hwork[threadIdx.x] = 0;
     __syncthreads();
     const int64_t count = min((int64_t)*num_pieces, pieces_cap);
     for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < count;
@@ -558,12 +442,13 @@ __global__ __launch_bounds__(256) void row_piece_finish_kernel(Pruned g, int32_t
             jm = max(jm, piece_jm[t + k]);
         }
         // a malformed member has already set err
-        plan_finish(g, r, q0, q1, w, jm, false, light_max, slot_work, o, ccount, &hwork, err);
+        plan_finish(g, r, q0, q1, w, jm, false, light_max, slot_work, o, ccount, hwork, err);
     }
     __syncthreads();
     if (threadIdx.x < kNumLists && ccount[threadIdx.x])
         atomicAdd(&class_count[threadIdx.x], ccount[threadIdx.x]);
-    if (threadIdx.x == 0 && hwork) atomicAdd(heavy_work, hwork);
+    if (threadIdx.x == 0 && hwork[0]) atomicAdd(heavy_work, hwork[0]);
+    if (threadIdx.x < 2 && hwork[1 + threadIdx.x]) atomicAdd(o.dense_work + threadIdx.x, hwork[1 + threadIdx.x]);
 }
 
 // A row block: rows outside [r0, r1) get no slots, no class and no boundary
@@ -580,9 +465,9 @@ __global__ __launch_bounds__(256) void block_mask_kernel(int64_t m, int64_t r0, 
                                                          unsigned long long *__restrict__ heavy_work,
                                                          unsigned long long *__restrict__ dense_work) {
     __shared__ unsigned long long cc[kNumLists];
-    __shared__ unsigned long long hw, dw;
+    __shared__ unsigned long long hw, dw, hr;
     if (threadIdx.x < kNumLists) cc[threadIdx.x] = 0;
-    if (threadIdx.x == 0) hw = dw = 0;
+    if (threadIdx.x == 0) hw = dw = hr = 0;
     __syncthreads();
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) {
@@ -594,12 +479,14 @@ __global__ __launch_bounds__(256) void block_mask_kernel(int64_t m, int64_t r0, 
         bsize[i] = in ? bsize_all[i] : 0;
         if (c != kNone) atomicAdd(&cc[c - 1], (unsigned long long)ns);
         if (c == kHeavy || c == kHeavyWide) atomicAdd(&hw, (unsigned long long)work[i]);
-        if (c == kDense) atomicAdd(&dw, (unsigned long long)work[i]);
+        if (c == kDense || c == kDenseHub) atomicAdd(&dw, (unsigned long long)work[i]);
+        if (c == kDenseHub) atomicAdd(&hr, 1ull);
     }
     __syncthreads();
     if (threadIdx.x < kNumLists && cc[threadIdx.x]) atomicAdd(&class_count[threadIdx.x], cc[threadIdx.x]);
     if (threadIdx.x == 0 && hw) atomicAdd(heavy_work, hw);
     if (threadIdx.x == 0 && dw) atomicAdd(dense_work, dw);
+    if (threadIdx.x == 0 && hr) atomicAdd(dense_work + 1, hr);
 }
 
 // Tier lists filled by fill_slots_kernel.
@@ -742,7 +629,7 @@ __global__ __launch_bounds__(256) void heavy_desc_kernel(
     const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x / 64);
     for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 64; i < m; i += nwaves) {
         const int cls = rclass[i];
-        if (cls < kHeavy) continue;
+        if (cls < kHeavy || cls == kDenseHub) continue;
         const int h = cls - kHeavy;  // list: heavy, heavy-wide, dense
         const int ns = nslots[i];
         const int64_t at = hat[h * (m + 1) + i];  // prefix of the class's slots
@@ -2855,8 +2742,8 @@ hipError_t launch_vs_cid(int64_t n, int64_t m, int64_t nnz, const int64_t *vs_pt
 }
 
 hipError_t launch_row_plan(const Pruned &g, int32_t s_min, int32_t light_max, int64_t slot_work, int64_t row_lo,
-                           int64_t row_hi, int32_t dense_ratio, int32_t dense_min, int32_t *tail_beg, int64_t *work,
-                           int32_t *jmax, int32_t *nslots, uint8_t *rclass, int64_t *bsize,
+                           int64_t row_hi, int32_t dense_ratio, int32_t dense_min, const HubInfo *hub, int32_t *tail_beg,
+                           int64_t *work, int32_t *jmax, int32_t *nslots, uint8_t *rclass, int64_t *bsize,
                            unsigned long long *class_count, int *err, unsigned long long *heavy_work,
                            unsigned long long *dense_work, int64_t *pieces, unsigned long long *num_pieces,
                            hipStream_t st) {
@@ -2864,7 +2751,7 @@ hipError_t launch_row_plan(const Pruned &g, int32_t s_min, int32_t light_max, in
     if (light_max <= 0 || light_max > kLightMax) light_max = kLightMax;
     if (slot_work <= 0) slot_work = kSlotWork;
     if (!g.cid) dense_ratio = 0;
-    const RowPlanOut o{tail_beg, work, jmax, nslots, rclass, bsize, dense_ratio, dense_min, dense_work};
+    const RowPlanOut o{tail_beg, work, jmax, nslots, rclass, bsize, dense_ratio, dense_min, hub, dense_work};
     row_plan_kernel<<<wave_grid((g.m + 63) / 64, 4, 8192), 256, 0, st>>>(g, s_min, light_max, slot_work, row_lo,
                                                                           row_hi, o,
                                                                           class_count, err, heavy_work, pieces,
