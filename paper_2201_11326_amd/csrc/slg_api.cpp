@@ -299,7 +299,7 @@ struct PlanBufs {
     uint8_t *flag = nullptr;
     int64_t *pos = nullptr, *part_nnz = nullptr, *vs_ptr = nullptr;
     int32_t *vs_idx = nullptr;
-    int32_t *tail_beg = nullptr, *jmax = nullptr, *nslots = nullptr, *slot_row = nullptr;
+    int32_t *tail_beg = nullptr, *tail_end = nullptr, *jmax = nullptr, *nslots = nullptr, *slot_row = nullptr;
     int64_t *work = nullptr, *work_pre = nullptr, *counters = nullptr, *part_m = nullptr;
     int64_t *bsize = nullptr, *bbase = nullptr, *hat = nullptr, *part_s = nullptr;
     int32_t *hcnt = nullptr;
@@ -639,7 +639,7 @@ hipError_t enqueue_rows(slg_plan *p, hipStream_t st) {
         StageTimer tm(ctx, kStRowPlan, st);
         if ((e = launch_row_plan(p->pr, p->s_min, p->light_max, p->slot_work, p->plan_lo,
                                  p->plan_hi < 0 ? m : p->plan_hi, p->dense ? p->dense_ratio : 0,
-                                 p->dense_min, p->hubs ? b.hub : nullptr, b.tail_beg, b.work, b.jmax, b.nslots, b.rclass, b.bsize,
+                                 p->dense_min, p->hubs ? b.hub : nullptr, b.tail_beg, b.tail_end, b.work, b.jmax, b.nslots, b.rclass, b.bsize,
                                  reinterpret_cast<unsigned long long *>(b.counters + kCntClass),
                                  reinterpret_cast<int *>(b.counters + kCntErr),
                                  reinterpret_cast<unsigned long long *>(b.counters + kCntHeavyWork),
@@ -872,6 +872,7 @@ slg_status plan_rows(slg_plan *p) {
         phase1.add(&b.vs_idx, nnz);
     }
     phase1.add(&b.tail_beg, nnz);
+    phase1.add(&b.tail_end, nnz);
     phase1.add(&b.work, m);
     phase1.add(&b.work_pre, m + 1);
     phase1.add(&b.jmax, m);
@@ -917,6 +918,7 @@ slg_status plan_rows(slg_plan *p) {
         b.hub_hist = b.counters + kCntHubHist;
     }
     pr.tail_beg = b.tail_beg;
+    pr.tail_end = b.tail_end;
     pr.cid = b.cid;
     pr.cid_row = b.cid_row;
     pr.vs_cid = b.vs_cid;

@@ -74,7 +74,8 @@ struct Pruned {
     const int32_t *he_idx;
     const int64_t *vs_ptr;    // vertex lists restricted to E_{s_min}
     const int32_t *vs_idx;
-    const int32_t *tail_beg;  // per incidence (i, v): first position in v's list after i
+    const int32_t *tail_beg;  // per incidence (i, v): first position in v's list after i,
+    const int32_t *tail_end;  // and the list's end
     const int32_t *row_s;     // per-row threshold (batched form), or null for s_min
     // E_s positions (the dense tier; null when the plan has none): cid[i] =
     // rank of row i among the kept rows (-1 if pruned), cid_row[c] = the row
@@ -192,7 +193,7 @@ hipError_t launch_vs_cid(int64_t n, int64_t m, int64_t nnz, const int64_t *vs_pt
 // slots); their member tails are not located.
 hipError_t launch_row_plan(const Pruned &g, int32_t s_min, int32_t light_max, int64_t slot_work, int64_t row_lo,
                            int64_t row_hi, int32_t dense_ratio, int32_t dense_min, const HubInfo *hub, int32_t *tail_beg,
-                           int64_t *work, int32_t *jmax, int32_t *nslots, uint8_t *rclass, int64_t *bsize,
+                           int32_t *tail_end, int64_t *work, int32_t *jmax, int32_t *nslots, uint8_t *rclass, int64_t *bsize,
                            unsigned long long *class_count, int *err, unsigned long long *heavy_work,
                            unsigned long long *dense_work, int64_t *pieces, unsigned long long *num_pieces,
                            hipStream_t st);

@@ -204,18 +204,22 @@ __device__ __forceinline__ int light_class(int64_t w) {
 }
 
 // Per-row work estimate (Section III-E's cost: the 2-paths of row i) and
-// tier. Rows of at most kSmallRow members are walked by one lane each, rows
-// of at most kWaveRow by the wavefront of their row group; larger rows are
-// cut into pieces of kPlanPiece members, one wavefront per piece, so that a
-// run of large rows (an input sorted by size) spreads over the whole grid. For every incidence (i, v) of a kept row: tail_beg = first
-// position after i in v's (pruned) list; w_i = sum of the tails; jm =
-// largest partner id.
-constexpr int kSmallRow = 16;
-constexpr int kWaveRow = 64;
+// tier. For every incidence (i, v) of a kept row: [tail_beg, tail_end) = the
+// part of v's (pruned) list after i; w_i = sum of the tails; jm = largest
+// partner id. Bound by the dependent loads of each incidence (the list's
+// bounds, then a binary search in it), so rows of at most kSmallRow members
+// are taken a group at a time by one wavefront, their members flattened: one
+// incidence per lane, kPlanAhead of them searched in lockstep. (One lane per
+// row walked its members one after another: 50 us on a thousand rows of 11,
+// 1.02 ms on the 8.8e6 rows of a batch.) Larger rows are cut into pieces of
+// kPlanPiece members, one wavefront per piece, so that a run of large rows
+// (an input sorted by size) spreads over the whole grid.
+constexpr int kSmallRow = 64;
 constexpr int kPlanPiece = 256;
+constexpr int kPlanAhead = 4;
 
 struct RowPlanOut {
-    int32_t *tail_beg;
+    int32_t *tail_beg, *tail_end;
     int64_t *work;
     int32_t *jmax;
     int32_t *nslots;
@@ -227,27 +231,60 @@ struct RowPlanOut {
     unsigned long long *dense_work;  // 2-paths of dense and hub rows, then the number of hub rows
 };
 
-// One member of row i: its tail in v's list; returns false when the
-// incidence is malformed.
-__device__ __forceinline__ bool plan_member(const Pruned &g, int64_t i, int64_t p, int32_t *tail_beg, int64_t &w,
-                                            int &jm) {
-    const int v = g.he_idx[p];
-    if (v < 0 || v >= g.n) {
-        tail_beg[p] = 0;
-        return false;
+// Members p[u] of rows i[u] (in[u]: this lane has one): their tails, the tail
+// lengths w and last partners jm (-1: none); bad: the incidence is malformed.
+__device__ __forceinline__ void plan_members(const Pruned &g, const int (&i)[kPlanAhead],
+                                             const int (&p)[kPlanAhead], const bool (&in)[kPlanAhead],
+                                             int32_t *__restrict__ tail_beg, int32_t *__restrict__ tail_end,
+                                             int (&w)[kPlanAhead], int (&jm)[kPlanAhead], bool (&bad)[kPlanAhead]) {
+    int v[kPlanAhead], a[kPlanAhead], e[kPlanAhead], hi[kPlanAhead];
+#pragma unroll
+    for (int u = 0; u < kPlanAhead; ++u) v[u] = in[u] ? g.he_idx[p[u]] : -1;
+#pragma unroll
+    for (int u = 0; u < kPlanAhead; ++u) {
+        int64_t l = 0, h = 0;
+        const bool id = v[u] >= 0 && v[u] < g.n;
+        if (id) {
+            l = g.vs_ptr[v[u]];
+            h = g.vs_ptr[v[u] + 1];
+        }
+        bad[u] = in[u] && (!id || l < 0 || h < l || h > g.nnz);
+        if (bad[u]) l = h = 0;
+        a[u] = (int)l;
+        e[u] = hi[u] = (int)h;
     }
-    const int64_t lo = g.vs_ptr[v], hi = g.vs_ptr[v + 1];
-    if (lo < 0 || hi < lo || hi > g.nnz) {
-        tail_beg[p] = 0;
-        return false;
+    bool more = true;
+    while (more) {
+        int mid[kPlanAhead], x[kPlanAhead];
+        more = false;
+#pragma unroll
+        for (int u = 0; u < kPlanAhead; ++u) {
+            mid[u] = (a[u] + e[u]) >> 1;
+            x[u] = a[u] < e[u] ? g.vs_idx[mid[u]] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < kPlanAhead; ++u) {
+            if (a[u] >= e[u]) continue;
+            if (x[u] < i[u])
+                a[u] = mid[u] + 1;
+            else
+                e[u] = mid[u];
+            more |= a[u] < e[u];
+        }
     }
-    const int a = lower_bound_i32(g.vs_idx, (int)lo, (int)hi, (int)i);
-    const bool found = a < hi && g.vs_idx[a] == (int)i;  // the vertex CSR must be the transpose
-    const int beg = found ? a + 1 : a;
-    tail_beg[p] = beg;
-    w += hi - beg;
-    if (beg < hi) jm = max(jm, g.vs_idx[hi - 1]);
-    return found;
+#pragma unroll
+    for (int u = 0; u < kPlanAhead; ++u) {
+        // the vertex CSR must be the transpose: i is in the list
+        const bool found = a[u] < hi[u] && g.vs_idx[a[u]] == i[u];
+        const int beg = found ? a[u] + 1 : a[u];
+        bad[u] |= in[u] && !found;
+        w[u] = hi[u] - beg;
+        jm[u] = beg < hi[u] ? g.vs_idx[hi[u] - 1] : -1;
+        if (in[u]) {
+            tail_beg[p[u]] = beg;
+            tail_end[p[u]] = hi[u];
+        }
+    }
 }
 
 // Tier, slot count and boundary-table size of row i from its totals. hwork
@@ -297,9 +334,11 @@ __device__ __forceinline__ void plan_finish(const Pruned &g, int64_t i, int64_t 
     if (cls == kDenseHub) atomicAdd(hwork + 2, 1ull);
 }
 
-// Small and middle rows, and the piece list of the large ones: a large row
-// appends ceil(size / kPlanPiece) entries (row | piece << 32), one row's
-// pieces side by side.
+// Small rows, ROWS of them per wavefront, and the piece list of the large
+// ones: a large row appends ceil(size / kPlanPiece) entries (row | piece <<
+// 32), one row's pieces side by side. ROWS: 64, or 16 where 64 would leave
+// the chip short of wavefronts.
+template <int ROWS>
 __global__ __launch_bounds__(256) void row_plan_kernel(Pruned g, int32_t s_min, int32_t light_max,
                                                        int64_t slot_work, int64_t row_lo, int64_t row_hi,
                                                        RowPlanOut o,
@@ -310,61 +349,81 @@ __global__ __launch_bounds__(256) void row_plan_kernel(Pruned g, int32_t s_min, 
                                                        unsigned long long *__restrict__ num_pieces) {
     __shared__ unsigned long long ccount[kNumLists];
     __shared__ unsigned long long hwork[3];
+    __shared__ int pre[4][64], pos[4][64], rjm[4][64], rbad[4][64];
+    __shared__ unsigned long long rw[4][64];
     if (threadIdx.x < kNumLists) ccount[threadIdx.x] = 0;
     if (threadIdx.x < 3) hwork[threadIdx.x] = 0;
     __syncthreads();
-    const int lane = lane_id();
+    const int lane = lane_id(), wv = threadIdx.x >> 6;
     const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x / 64);
-    for (int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 64 * 64; i0 < g.m; i0 += nwaves * 64) {
+    for (int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 64 * ROWS; i0 < g.m; i0 += nwaves * ROWS) {
         const int64_t i = i0 + lane;
         unsigned long long np = 0;  // pieces of a large row
-        bool mid = false;           // a middle row, walked by the wavefront below
-        if (i < g.m) {
-            const int64_t p0 = g.he_ptr[i], p1 = g.he_ptr[i + 1];
-            if (p0 < 0 || p1 > g.nnz || p1 < p0) {  // malformed pointers
-                plan_finish(g, i, p0, p1, 0, -1, true, light_max, slot_work, o, ccount, hwork, err);
-            } else {
-                const int64_t size = p1 - p0;
-                // rows outside [row_lo, row_hi) are planned as pruned ones
-                const bool kept = size > 0 && size >= (g.row_s ? g.row_s[i] : s_min) && i >= row_lo && i < row_hi;
-                if (kept && size > kWaveRow) {
-                    np = (unsigned long long)((size + kPlanPiece - 1) / kPlanPiece);
-                } else if (kept && size > kSmallRow) {
-                    mid = true;
-                } else {  // a small (or pruned) row, walked by its own lane
-                    int64_t w = 0;
-                    int jm = -1;
-                    bool rbad = false;
-                    if (kept)
-                        for (int64_t p = p0; p < p1; ++p) rbad |= !plan_member(g, i, p, o.tail_beg, w, jm);
-                    plan_finish(g, i, p0, p1, w, jm, rbad, light_max, slot_work, o, ccount, hwork, err);
+        int64_t p0 = 0, p1 = 0;
+        int n = 0;           // members of a small kept row
+        bool own = false;    // this lane finishes its row
+        bool broken = false;
+        if (lane < ROWS && i < g.m) {
+            p0 = g.he_ptr[i];
+            p1 = g.he_ptr[i + 1];
+            broken = p0 < 0 || p1 > g.nnz || p1 < p0;  // malformed pointers
+            const int64_t size = broken ? 0 : p1 - p0;
+            // rows outside [row_lo, row_hi) are planned as pruned ones
+            const bool kept = size > 0 && size >= (g.row_s ? g.row_s[i] : s_min) && i >= row_lo && i < row_hi;
+            if (kept && size > kSmallRow)
+                np = (unsigned long long)((size + kPlanPiece - 1) / kPlanPiece);
+            else
+                own = true;
+            n = kept && own ? (int)size : 0;
+        }
+        const int incl = wave_incl_scan(n);
+        const int total = __builtin_amdgcn_readlane(incl, 63);
+        pre[wv][lane] = incl - n;
+        pos[wv][lane] = (int)p0;
+        rw[wv][lane] = 0;
+        rjm[wv][lane] = -1;
+        rbad[wv][lane] = 0;
+        wave_lds_sync();
+        for (int f0 = 0; f0 < total; f0 += 64 * kPlanAhead) {
+            int row[kPlanAhead], id[kPlanAhead], p[kPlanAhead], w[kPlanAhead], jm[kPlanAhead];
+            bool in[kPlanAhead], bad[kPlanAhead];
+#pragma unroll
+            for (int u = 0; u < kPlanAhead; ++u) row[u] = 0;
+#pragma unroll
+            for (int step = ROWS / 2; step > 0; step >>= 1)  // largest row with pre <= f
+#pragma unroll
+                for (int u = 0; u < kPlanAhead; ++u)
+                    if (pre[wv][row[u] + step] <= f0 + 64 * u + lane) row[u] += step;
+#pragma unroll
+            for (int u = 0; u < kPlanAhead; ++u) {
+                const int f = f0 + 64 * u + lane;
+                in[u] = f < total;
+                id[u] = (int)i0 + row[u];
+                p[u] = pos[wv][row[u]] + (f - pre[wv][row[u]]);
+            }
+            plan_members(g, id, p, in, o.tail_beg, o.tail_end, w, jm, bad);
+#pragma unroll
+            for (int u = 0; u < kPlanAhead; ++u) {
+                if (!in[u]) continue;
+                if (w[u] > 0) {
+                    atomicAdd(&rw[wv][row[u]], (unsigned long long)w[u]);
+                    atomicMax(&rjm[wv][row[u]], jm[u]);
                 }
+                if (bad[u]) rbad[wv][row[u]] = 1;
             }
         }
-        // the middle rows of this group, one after another by the whole
-        // wavefront (one member per lane)
-        unsigned long long todo = __ballot(mid);
-        while (todo) {
-            const int l = __ffsll((long long)todo) - 1;
-            todo &= todo - 1;
-            const int64_t r = i0 + l;
-            const int64_t q0 = g.he_ptr[r], q1 = g.he_ptr[r + 1];
-            int64_t w = 0;
-            int jm = -1;
-            int rbad = 0;
-            if (q0 + lane < q1) rbad = !plan_member(g, r, q0 + lane, o.tail_beg, w, jm);
-            w = wave_sum(w);
-            jm = wave_max(jm);
-            rbad = wave_max(rbad);
-            if (lane == 0) plan_finish(g, r, q0, q1, w, jm, rbad != 0, light_max, slot_work, o, ccount, hwork, err);
-        }
+        wave_lds_sync();
+        if (own)
+            plan_finish(g, i, p0, p1, (int64_t)rw[wv][lane], rjm[wv][lane], broken || rbad[wv][lane] != 0, light_max,
+                        slot_work, o, ccount, hwork, err);
+        wave_lds_sync();
         // one reservation per wavefront for the pieces of its large rows
-        const unsigned long long incl = wave_incl_scan(np);
-        const unsigned long long total = __shfl(incl, 63);
-        if (total) {
+        const unsigned long long pincl = wave_incl_scan(np);
+        const unsigned long long ptotal = __shfl(pincl, 63);
+        if (ptotal) {
             unsigned long long base = 0;
-            if (lane == 0) base = atomicAdd(num_pieces, total);
-            base = __shfl(base, 0) + incl - np;
+            if (lane == 0) base = atomicAdd(num_pieces, ptotal);
+            base = __shfl(base, 0) + pincl - np;
             // within the capacity unless the row pointers overlap (malformed)
             for (unsigned long long k = 0; k < np; ++k) {
                 if (base + k < (unsigned long long)pieces_cap)
@@ -384,6 +443,7 @@ __global__ __launch_bounds__(256) void row_plan_kernel(Pruned g, int32_t s_min, 
 // One wavefront per piece of a large row: the piece's tails and its largest
 // partner id, into the piece's own partial slots.
 __global__ __launch_bounds__(256) void row_piece_kernel(Pruned g, int32_t *__restrict__ tail_beg,
+                                                        int32_t *__restrict__ tail_end,
                                                         const int64_t *__restrict__ pieces, int64_t pieces_cap,
                                                         const unsigned long long *__restrict__ num_pieces,
                                                         int64_t *__restrict__ piece_w,
@@ -398,7 +458,23 @@ __global__ __launch_bounds__(256) void row_piece_kernel(Pruned g, int32_t *__res
         const int64_t a = q0 + k * kPlanPiece, b = min(q1, a + kPlanPiece);
         int64_t w = 0;
         int jm = -1, rbad = 0;
-        for (int64_t p = a + lane; p < b; p += 64) rbad |= !plan_member(g, r, p, tail_beg, w, jm);
+        static_assert(kPlanPiece == 64 * kPlanAhead, "a piece in one go");
+        int id[kPlanAhead], p[kPlanAhead], wu[kPlanAhead], ju[kPlanAhead];
+        bool in[kPlanAhead], bu[kPlanAhead];
+#pragma unroll
+        for (int u = 0; u < kPlanAhead; ++u) {
+            id[u] = (int)r;
+            p[u] = (int)a + 64 * u + lane;
+            in[u] = p[u] < b;
+        }
+        plan_members(g, id, p, in, tail_beg, tail_end, wu, ju, bu);
+#pragma unroll
+        for (int u = 0; u < kPlanAhead; ++u) {
+            if (!in[u]) continue;
+            w += wu[u];
+            jm = max(jm, ju[u]);
+            rbad |= bu[u] ? 1 : 0;
+        }
         w = wave_sum(w);
         jm = wave_max(jm);
         rbad = wave_max(rbad);
@@ -566,7 +642,6 @@ __global__ __launch_bounds__(256) void fill_slots_kernel(
     }
 }
 
-// One wavefront per heavy row, one lane per slot: the slot descriptors.
 // Heavy slots per row, by class: the prefix sums place every heavy row's
 // descriptors in row order, so each heavy list is in slot order.
 __global__ void heavy_counts_kernel(int64_t m, const uint8_t *__restrict__ rclass, const int32_t *__restrict__ nslots,
@@ -614,6 +689,7 @@ __global__ void heavy_range_kernel(const HeavyDesc *__restrict__ desc, int64_t c
     out[threadIdx.x] = lo;
 }
 
+// The slot descriptors of the heavy rows, one lane per slot.
 struct HeavyLists {
     HeavyDesc *l[kNumHeavyLists];  // heavy, heavy-wide, dense
     int64_t cap[kNumHeavyLists];
@@ -627,40 +703,59 @@ __global__ __launch_bounds__(256) void heavy_desc_kernel(
     const int32_t *__restrict__ cid, int *__restrict__ err) {
     const int lane = lane_id();
     const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x / 64);
-    for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 64; i < m; i += nwaves) {
-        const int cls = rclass[i];
-        if (cls < kHeavy || cls == kDenseHub) continue;
-        const int h = cls - kHeavy;  // list: heavy, heavy-wide, dense
-        const int ns = nslots[i];
-        const int64_t at = hat[h * (m + 1) + i];  // prefix of the class's slots
-        if (at < 0 || at + ns > hl.cap[h]) {
-            if (lane == 0) atomicOr(err, 16);
-            continue;
+    // 64 rows per wavefront: each lane loads its own row's values, then the
+    // heavy rows among them are written one after another (a wavefront per
+    // row spent 0.43 ms on the classes of 8.8e6 rows)
+    for (int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 64 * 64; i0 < m; i0 += nwaves * 64) {
+        const int64_t own = i0 + lane;
+        const int own_cls = own < m ? rclass[own] : kNone;
+        const bool heavy = own_cls >= kHeavy && own_cls != kDenseHub;
+        int own_ns = 0, own_k = 0, own_range = 0, own_w0 = 0, own_base = 0;
+        int64_t own_at = 0, own_bb = 0;
+        if (heavy) {
+            own_ns = nslots[own];
+            own_at = hat[(own_cls - kHeavy) * (m + 1) + own];  // prefix of the class's slots
+            own_base = (int32_t)slot_base[own];
+            own_range = (int32_t)(jmax[own] - own);
+            own_k = (int)(he_ptr[own + 1] - he_ptr[own]);
+            own_bb = bbase[own];
+            // dense slots: aligned windows of E_s positions from the window of
+            // the row's first candidate (its own position + 1)
+            own_w0 = own_cls == kDense ? (cid[own] + 1) >> kDenseBits : 0;
         }
-        HeavyDesc *lst = hl.l[h] + at;
-        const int64_t base = slot_base[i];
-        const int64_t range = (int64_t)jmax[i] - i;
-        const int k = (int)(he_ptr[i + 1] - he_ptr[i]);
-        const int64_t bb = bbase[i];
-        // dense slots: aligned windows of E_s positions from the window of
-        // the row's first candidate (its own position + 1)
-        const int64_t w0 = cls == kDense ? ((int64_t)cid[i] + 1) >> kDenseBits : 0;
-        for (int t = lane; t < ns; t += 64) {
-            HeavyDesc d;
-            d.row = (int32_t)i;
-            if (cls == kDense) {
-                d.ja = (int32_t)((w0 + t) << kDenseBits);
-                d.jb = (int32_t)((w0 + t + 1) << kDenseBits);
-            } else {
-                d.ja = (int32_t)(i + 1 + range * t / ns);
-                d.jb = (int32_t)(i + 1 + range * (t + 1) / ns);
+        unsigned long long todo = __ballot(heavy);
+        while (todo) {
+            const int l = __ffsll((long long)todo) - 1;
+            todo &= todo - 1;
+            auto of = [&](int x) { return __builtin_amdgcn_readlane(x, l); };
+            auto of64 = [&](int64_t x) {
+                return (int64_t)((uint64_t)(uint32_t)of((int)(x >> 32)) << 32 | (uint32_t)of((int)x));
+            };
+            const int i = (int)i0 + l, cls = of(own_cls), h = cls - kHeavy;  // list: heavy, heavy-wide, dense
+            const int ns = of(own_ns), k = of(own_k), w0 = of(own_w0), base = of(own_base);
+            const int64_t at = of64(own_at), bb = of64(own_bb), range = of(own_range);
+            if (at < 0 || at + ns > hl.cap[h]) {
+                if (lane == 0) atomicOr(err, 16);
+                continue;
             }
-            d.k = k;
-            d.slot = (int32_t)(base + t);
-            d.last = t == ns - 1;
-            d.bptr = bb + (int64_t)t * k;
-            slot_row[base + t] = (int32_t)i;
-            lst[t] = d;
+            HeavyDesc *lst = hl.l[h] + at;
+            for (int t = lane; t < ns; t += 64) {
+                HeavyDesc d;
+                d.row = i;
+                if (cls == kDense) {
+                    d.ja = (w0 + t) << kDenseBits;
+                    d.jb = (w0 + t + 1) << kDenseBits;
+                } else {
+                    d.ja = (int32_t)(i + 1 + range * t / ns);
+                    d.jb = (int32_t)(i + 1 + range * (t + 1) / ns);
+                }
+                d.k = k;
+                d.slot = base + t;
+                d.last = t == ns - 1;
+                d.bptr = bb + (int64_t)t * k;
+                slot_row[base + t] = i;
+                lst[t] = d;
+            }
         }
     }
 }
@@ -725,9 +820,8 @@ __global__ __launch_bounds__(256) void tiny_kernel(const int32_t *__restrict__ l
     const int64_t p0 = g.he_ptr[i], p1 = g.he_ptr[i + 1];
     int n = 0;
     for (int64_t p = p0; p < p1 && n < kTinyMax; ++p) {
-        const int v = g.he_idx[p];
-        const int64_t end = g.vs_ptr[v + 1];
-        for (int64_t q = g.tail_beg[p]; q < end && n < kTinyMax; ++q) keys[n++][tid] = g.vs_idx[q];
+        const int end = g.tail_end[p];
+        for (int q = g.tail_beg[p]; q < end && n < kTinyMax; ++q) keys[n++][tid] = g.vs_idx[q];
     }
     int k[kTinyMax];
 #pragma unroll
@@ -818,9 +912,8 @@ __global__ __launch_bounds__(256) void light_kernel(const int32_t *__restrict__ 
         const int64_t p = q + lane;
         int beg = 0, len = 0;
         if (p < p1) {
-            const int v = g.he_idx[p];
             beg = g.tail_beg[p];
-            len = (int)(g.vs_ptr[v + 1] - beg);
+            len = g.tail_end[p] - beg;
         }
         const int incl = wave_incl_scan(len);
         const int tot = __shfl(incl, 63);
@@ -1768,9 +1861,8 @@ __global__ __launch_bounds__(256) void heavy_edges_kernel(const HeavyDesc *__res
 // lower bound; quick tests skip the search when the tail misses the slot.
 __global__ __launch_bounds__(256) void bounds_kernel(
     const HeavyDesc *__restrict__ desc, int64_t count, const int64_t *__restrict__ he_ptr,
-    const int32_t *__restrict__ he_idx, const int64_t *__restrict__ vs_ptr,
     const int32_t *__restrict__ vs_idx, const int32_t *__restrict__ tail_beg,
-    int32_t *__restrict__ bounds) {
+    const int32_t *__restrict__ tail_end, int32_t *__restrict__ bounds) {
     // workgroups are dealt to the 8 XCDs in turn; each XCD takes runs of 16
     // consecutive blocks (64 slots) instead, so that a row's slots (which
     // search the same vertex lists) mostly share one L2, while the runs
@@ -1786,9 +1878,8 @@ __global__ __launch_bounds__(256) void bounds_kernel(
     const int64_t p0 = he_ptr[d.row];
     for (int q = lane; q < d.k; q += 64) {
         const int64_t p = p0 + q;
-        const int v = he_idx[p];
         const int beg = tail_beg[p];
-        const int end = (int)vs_ptr[v + 1];
+        const int end = tail_end[p];
         int val = beg;
         if (beg < end && vs_idx[beg] < d.ja)
             val = vs_idx[end - 1] < d.ja ? end : lower_bound_i32(vs_idx, beg, end, d.ja);
@@ -2653,11 +2744,11 @@ inline unsigned wave_grid(int64_t rows, int waves_per_block, int64_t cap) {
 // ---------------------------------------------------------------------------
 int64_t scan_partials_size(int64_t n) { return (n + kScanTile - 1) / kScanTile + 1; }
 
-// A large row of S > kWaveRow >= kSmallRow members has ceil(S / 256) <=
-// (S + 255) / 256 <= S / 16 pieces (S >= 17): at most nnz / 16 in all when
+// A large row of S > kSmallRow members has ceil(S / 256) <= (S + 255) / 256
+// <= S / 16 pieces (S >= 17): at most nnz / 16 in all when
 // the rows do not overlap. The piece list holds, per piece, its entry, its 2-paths (int64)
 // and its largest partner (int32): 3 * cap int64 in all.
-static_assert(kPlanPiece == 256 && kWaveRow >= kSmallRow && kSmallRow >= 16 && kWaveRow <= 64, "piece bound");
+static_assert(kPlanPiece == 256 && kSmallRow >= 16 && kSmallRow <= 64, "piece bound");
 int64_t plan_pieces_cap(int64_t nnz) { return nnz / 16 + 1; }
 
 int heavy_resident(int device) {
@@ -2743,7 +2834,7 @@ hipError_t launch_vs_cid(int64_t n, int64_t m, int64_t nnz, const int64_t *vs_pt
 
 hipError_t launch_row_plan(const Pruned &g, int32_t s_min, int32_t light_max, int64_t slot_work, int64_t row_lo,
                            int64_t row_hi, int32_t dense_ratio, int32_t dense_min, const HubInfo *hub, int32_t *tail_beg,
-                           int64_t *work, int32_t *jmax, int32_t *nslots, uint8_t *rclass, int64_t *bsize,
+                           int32_t *tail_end, int64_t *work, int32_t *jmax, int32_t *nslots, uint8_t *rclass, int64_t *bsize,
                            unsigned long long *class_count, int *err, unsigned long long *heavy_work,
                            unsigned long long *dense_work, int64_t *pieces, unsigned long long *num_pieces,
                            hipStream_t st) {
@@ -2751,16 +2842,22 @@ hipError_t launch_row_plan(const Pruned &g, int32_t s_min, int32_t light_max, in
     if (light_max <= 0 || light_max > kLightMax) light_max = kLightMax;
     if (slot_work <= 0) slot_work = kSlotWork;
     if (!g.cid) dense_ratio = 0;
-    const RowPlanOut o{tail_beg, work, jmax, nslots, rclass, bsize, dense_ratio, dense_min, hub, dense_work};
-    row_plan_kernel<<<wave_grid((g.m + 63) / 64, 4, 8192), 256, 0, st>>>(g, s_min, light_max, slot_work, row_lo,
-                                                                          row_hi, o,
-                                                                          class_count, err, heavy_work, pieces,
-                                                                          plan_pieces_cap(g.nnz), num_pieces);
+    const RowPlanOut o{tail_beg, tail_end, work, jmax, nslots, rclass, bsize, dense_ratio, dense_min, hub, dense_work};
+    auto plan = [&](auto kernel, int rows) {
+        kernel<<<wave_grid((g.m + rows - 1) / rows, 4, 8192), 256, 0, st>>>(
+            g, s_min, light_max, slot_work, row_lo, row_hi, o, class_count, err, heavy_work, pieces,
+            plan_pieces_cap(g.nnz), num_pieces);
+    };
+    // 64 rows per wavefront fill the chip from about 2^17 rows on
+    if (g.m >= (1 << 17))
+        plan(row_plan_kernel<64>, 64);
+    else
+        plan(row_plan_kernel<16>, 16);
     // the piece count is known on the device only: grids for the bound
     const int64_t cap = plan_pieces_cap(g.nnz);
     int64_t *piece_w = pieces + cap;
     int32_t *piece_jm = reinterpret_cast<int32_t *>(pieces + 2 * cap);
-    row_piece_kernel<<<wave_grid(cap, 4, 4096), 256, 0, st>>>(g, tail_beg, pieces, cap, num_pieces, piece_w,
+    row_piece_kernel<<<wave_grid(cap, 4, 4096), 256, 0, st>>>(g, tail_beg, tail_end, pieces, cap, num_pieces, piece_w,
                                                               piece_jm, err);
     row_piece_finish_kernel<<<grid_for(cap, 256), 256, 0, st>>>(g, light_max, slot_work, o, class_count, err,
                                                                 heavy_work, pieces, cap, num_pieces, piece_w,
@@ -2790,7 +2887,7 @@ hipError_t launch_fill_slots(int64_t m, const int64_t *he_ptr, const int64_t *sl
         hl.l[h] = heavy[h];
         hl.cap[h] = caps[kLightClasses + h];
     }
-    heavy_desc_kernel<<<wave_grid(m, 4, 8192), 256, 0, st>>>(m, he_ptr, slot_base, nslots, jmax, rclass,
+    heavy_desc_kernel<<<wave_grid((m + 63) / 64, 4, 8192), 256, 0, st>>>(m, he_ptr, slot_base, nslots, jmax, rclass,
                                                               bbase, hat, slot_row, hl, cid, err);
     return hipGetLastError();
 }
@@ -2979,8 +3076,8 @@ hipError_t launch_heavy_edges(const HeavyDesc *desc, int64_t count, const int64_
 hipError_t launch_bounds(const Pruned &g, const HeavyDesc *desc, int64_t count, int32_t *bounds,
                          hipStream_t st) {
     if (count <= 0) return hipSuccess;
-    bounds_kernel<<<grid_for(count, 4), 256, 0, st>>>(desc, count, g.he_ptr, g.he_idx, g.vs_ptr, g.vs_idx,
-                                                       g.tail_beg, bounds);
+    bounds_kernel<<<grid_for(count, 4), 256, 0, st>>>(desc, count, g.he_ptr, g.vs_idx, g.tail_beg, g.tail_end,
+                                                       bounds);
     return hipGetLastError();
 }
 
