@@ -127,10 +127,11 @@ __global__ __launch_bounds__(512) void hub_select_kernel(int64_t n, const int64_
     if (tid == 0) {
         const double every = (double)load(&info->all_paths), rest = every - (double)hub_paths;
         const double rows = (double)*kept;
-        const double per_pair = rows > 0 ? rest / (0.5 * rows * rows) : 1.0;
+        const double pairs = 0.5 * rows * rows, per_pair = rows > 0 ? rest / pairs : 1.0;
         info->min_degree = lowest;
         info->hub_paths = hub_paths;
-        info->use = every >= kHubMinPaths && rest <= 0.125 * every && per_pair <= kHubMaxRest;
+        info->use = every >= kHubMinPaths && every >= kHubMinMean * pairs && rest <= 0.125 * every &&
+                    per_pair <= kHubMaxRest;
     }
 }
 

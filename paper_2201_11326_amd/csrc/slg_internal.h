@@ -37,6 +37,13 @@ constexpr int kHubMaxMembers = 255;   // overlaps of hub rows fit 8 bits
 constexpr int kHubRows = 32;
 constexpr double kHubMinPaths = double(1 << 28);  // fewest 2-paths of the graph for which its setup pays
 constexpr double kHubMaxRest = 0.125;  // most 2-paths outside the hubs per pair of kept rows
+// A row's products cost the same for every candidate, the walk of the dense
+// tier goes by its 2-paths: 1.5 ps a candidate (300 000 hyperedges of skewed
+// sizes, count and emit) against 0.7 ps a 2-path. Graphs far below that on
+// average have too few such rows for a group of them (200 000 hyperedges, 148
+// dense rows: 4.2 ms without the tier, 6.5 ms with it).
+constexpr int kHubMinRatio = 2;         // fewest 2-paths per candidate of a hub row
+constexpr double kHubMinMean = 0.25;    // and per pair of kept rows on average
 constexpr long long kDenseChunk = 1 << 16;  // dense-store entries a workgroup takes at a time
 
 // Row classes written by the planning kernel.

@@ -312,7 +312,7 @@ __device__ __forceinline__ void plan_finish(const Pruned &g, int64_t i, int64_t 
             cls = kLight0 + light_class(w);
             ns = 1;
         } else if (ci >= 0 && cj > ci && crange >= o.dense_min && 8 * w >= (int64_t)o.dense_ratio * crange) {
-            cls = o.hub && o.hub->use && p1 - p0 <= kHubMaxMembers ? kDenseHub : kDense;
+            cls = o.hub && o.hub->use && p1 - p0 <= kHubMaxMembers && w >= kHubMinRatio * crange ? kDenseHub : kDense;
             ns = (cj >> kDenseBits) - ((ci + 1) >> kDenseBits) + 1;
         } else {
             cls = (p1 - p0 >= kWideMembers) ? kHeavyWide : kHeavy;

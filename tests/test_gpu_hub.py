@@ -124,3 +124,13 @@ def test_stream_chunks_and_row_ranges():
                 assert torch.equal(torch.cat([c[t] for c in got[lg.s]]), getattr(lg, f)), (lg.s, f)
     g.release()
     ctx.close()
+
+
+@pytest.mark.parametrize("m, hubs, p, s, hub", [
+    (20_000, 60, 0.2, 5, True),    # rows on both sides of two 2-paths per candidate
+    (64_000, 100, 0.045, 3, False),  # 0.2 2-paths per pair of rows on average
+])
+def test_rows_and_graphs_below_the_tiers_ratio(m, hubs, p, s, hub):
+    ctx, g, _ = check(hub_graph(m, hubs=hubs, p=p, extra=2, seed=m), [s], hub=hub)
+    g.release()
+    ctx.close()
