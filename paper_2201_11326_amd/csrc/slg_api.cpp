@@ -300,7 +300,7 @@ struct PlanBufs {
     int64_t *pos = nullptr, *part_nnz = nullptr, *vs_ptr = nullptr;
     int32_t *vs_idx = nullptr;
     int32_t *tail_beg = nullptr, *tail_end = nullptr, *jmax = nullptr, *nslots = nullptr, *slot_row = nullptr;
-    int64_t *work = nullptr, *work_pre = nullptr, *counters = nullptr, *part_m = nullptr;
+    int64_t *work = nullptr, *work_pre = nullptr, *counters = nullptr, *part_m = nullptr, *part_light = nullptr;
     int64_t *bsize = nullptr, *bbase = nullptr, *hat = nullptr, *part_s = nullptr;
     int32_t *hcnt = nullptr;
     int64_t *pieces = nullptr;
@@ -342,7 +342,8 @@ struct slg_plan {
     int64_t S = 0;                 // number of slots
     Slots slots{};
     int32_t *bounds = nullptr;
-    int64_t *tickets = nullptr;    // work counters of the persistent heavy launches
+    int64_t *tickets = nullptr;    // work counters of the persistent heavy launches, then the tier lists
+    int64_t list_words = 0;        // of both
     HeavyDesc *heavy[kNumHeavyLists] = {};  // heavy, heavy-wide and dense slot descriptors
     int32_t *lists[kNumLists] = {};
     int64_t list_count[kNumLists] = {};
@@ -649,9 +650,8 @@ hipError_t enqueue_rows(slg_plan *p, hipStream_t st) {
             return e;
     }
     StageTimer tm(ctx, kStPlanScans, st);
-    if ((e = launch_exclusive_scan_i32(b.nslots, m, p->slot_base, b.part_m, st)) != hipSuccess) return e;
-    if ((e = launch_exclusive_scan_i64(b.work, m, b.work_pre, b.part_m, st)) != hipSuccess) return e;
-    return launch_exclusive_scan_i64(b.bsize, m, b.bbase, b.part_m, st);
+    return launch_scans(
+        ScanJobs().add(b.nslots, m, p->slot_base).add(b.work, m, b.work_pre).add(b.bsize, m, b.bbase), b.part_m, st);
 }
 
 // Slot table, tier lists, boundary table, counting pass and its scans.
@@ -719,14 +719,9 @@ hipError_t enqueue_slots_count(slg_plan *p, hipStream_t st) {
     PlanBufs &b = p->b;
     hipError_t e;
     // lists start zeroed: an entry the fill kernels refuse to write (list
-    // overflow, flagged in err) names slot 0 / an empty descriptor
-    for (int c = 0; c < kLightClasses; ++c)
-        if ((e = launch_fill_i32(p->lists[c], p->list_count[c], 0, st)) != hipSuccess) return e;
-    for (int h = 0; h < kNumHeavyLists; ++h)
-        if ((e = launch_fill_i64(reinterpret_cast<int64_t *>(p->heavy[h]),
-                                 p->list_count[kLightClasses + h] * (int64_t)(sizeof(HeavyDesc) / 8), 0, st)) !=
-            hipSuccess)
-            return e;
+    // overflow, flagged in err) names slot 0 / an empty descriptor; the
+    // counters of the later launches lie before them
+    if ((e = launch_fill_i64(p->tickets, p->list_words, 0, st)) != hipSuccess) return e;
     {
         StageTimer tm(ctx, kStSlots, st);
         // room of every list as planned (less the error-path tests' shortfall
@@ -735,7 +730,7 @@ hipError_t enqueue_slots_count(slg_plan *p, hipStream_t st) {
         for (int c = 0; c < kNumLists; ++c)
             caps[c] = c < kLightClasses ? p->list_count[c] : std::max<int64_t>(0, p->list_count[c] - p->list_shortfall);
         if ((e = launch_fill_slots(m, p->pr.he_ptr, p->slot_base, b.nslots, b.jmax, b.rclass, b.bbase, b.cid,
-                                   b.hat, b.hcnt, b.part_m, b.slot_row, p->lists, p->heavy, caps,
+                                   b.hat, b.hcnt, b.part_m, b.slot_row, p->lists, p->heavy, caps, p->list_count,
                                    reinterpret_cast<unsigned long long *>(b.counters + kCntFill),
                                    reinterpret_cast<int *>(b.counters + kCntErr), st)) != hipSuccess)
             return e;
@@ -751,7 +746,7 @@ hipError_t enqueue_slots_count(slg_plan *p, hipStream_t st) {
         StageTimer tm(ctx, kStCountLight, lst);
         if (p->use_lstore) {  // the light store's layout
             if ((e = launch_light_work(m, b.rclass, b.work, p->lwork, lst)) != hipSuccess) return e;
-            if ((e = launch_exclusive_scan_i32(p->lwork, m, p->lstore.off, b.part_m, lst)) != hipSuccess) return e;
+            if ((e = launch_exclusive_scan_i32(p->lwork, m, p->lstore.off, b.part_light, lst)) != hipSuccess) return e;
         }
         for (int c = 0; c < kLightClasses; ++c)
             if ((e = launch_light(c, false, p->lists[c], p->list_count[c], p->slots, p->pr, p->prm, p->slot_cnt,
@@ -777,7 +772,6 @@ hipError_t enqueue_slots_count(slg_plan *p, hipStream_t st) {
     // joined before the heavy counting pass: its persistent grid fills every
     // CU, and light workgroups still resident would hold some of it back
     if ((e = fork.join()) != hipSuccess) return e;
-    if ((e = launch_fill_i64(p->tickets, kTkTotal, 0, st)) != hipSuccess) return e;
     for (int wide = 0; wide < 2; ++wide) {
         if (p->list_count[kLightClasses + wide] <= 0) continue;
         StageTimer tm(ctx, wide ? kStCountHeavyWide : kStCountHeavy, st);
@@ -824,11 +818,10 @@ hipError_t enqueue_slots_count(slg_plan *p, hipStream_t st) {
             return e;
     }
     StageTimer tm(ctx, kStCountScans, st);
+    ScanJobs jobs;
     for (int k = 0; k < p->prm.k; ++k)
-        if ((e = launch_exclusive_scan_i64(p->slot_cnt + (size_t)k * p->S, p->S,
-                                           p->slot_off + (size_t)k * (p->S + 1), b.part_s, st)) != hipSuccess)
-            return e;
-    return hipSuccess;
+        jobs.add(p->slot_cnt + (size_t)k * p->S, p->S, p->slot_off + (size_t)k * (p->S + 1));
+    return launch_scans(jobs, b.part_s, st);
 }
 
 #define BUILD_HIP(call)                                                                            \
@@ -862,7 +855,8 @@ slg_status plan_rows(slg_plan *p) {
     p->prune = (p->s_min > 1 || pr.row_s) && nnz > 0;
     // the dense tier works in E_s positions; the batched form (a threshold
     // per row) keeps to the other tiers
-    p->dense = p->dense_ratio > 0 && !pr.row_s && nnz > 0 && m > 0;
+    // (a row has at most m - 1 candidates)
+    p->dense = p->dense_ratio > 0 && !pr.row_s && nnz > 0 && m > p->dense_min;
     AllocList phase1;
     if (p->prune) {
         phase1.add(&b.flag, nnz);
@@ -899,7 +893,8 @@ slg_status plan_rows(slg_plan *p) {
     }
     phase1.add(&b.counters, p->hubs ? kCntHubHist + hub_hist_words() : kCntRoom);
     phase1.add(&b.pieces, 3 * plan_pieces_cap(nnz));
-    phase1.add(&b.part_m, scan_partials_size(m));
+    phase1.add(&b.part_m, 3 * scan_partials_size(m));
+    phase1.add(&b.part_light, scan_partials_size(m));
     phase1.add(&p->slot_base, m + 1);
     if (p->reserve) {
         if (!(*p->reserve)(phase1.bytes)) return fail(ctx, SLG_ERR_OUT_OF_MEMORY, "device-memory budget refused");
@@ -930,11 +925,11 @@ slg_status plan_rows(slg_plan *p) {
         BUILD_HIP(hipMemcpyAsync(b.bsize_all, b.bsize, m * sizeof(int64_t), hipMemcpyDeviceToDevice, st));
     }
     int64_t *hb = ctx->pinned;
-    BUILD_HIP(hipMemcpyAsync(hb, b.counters, kCntTotal * sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    BUILD_HIP(hipMemcpyAsync(hb + kHbSlots, p->slot_base + m, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    BUILD_HIP(hipMemcpyAsync(hb + kHbSlots + 1, b.work_pre + m, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    BUILD_HIP(hipMemcpyAsync(hb + kHbSlots + 2, b.bbase + m, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    if (p->dense) BUILD_HIP(hipMemcpyAsync(hb + kHbRange + 1, b.kpre + m, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    ReadBack rb;
+    rb.add(b.counters, 0, kCntTotal).add(p->slot_base + m, kHbSlots).add(b.work_pre + m, kHbSlots + 1);
+    rb.add(b.bbase + m, kHbSlots + 2);
+    if (p->dense) rb.add(b.kpre + m, kHbRange + 1);
+    BUILD_HIP(launch_read_back(rb, hb, st));
     BUILD_HIP(hipStreamSynchronize(st));
     p->kept_rows = p->dense ? hb[kHbRange + 1] : 0;
     if (hb[kCntErr] & 0xffffffff)
@@ -973,13 +968,14 @@ slg_status plan_block(slg_plan *p, int64_t r0, int64_t r1) {
                                     b.bsize, reinterpret_cast<unsigned long long *>(b.counters + kCntClass),
                                     reinterpret_cast<unsigned long long *>(b.counters + kCntHeavyWork),
                                     reinterpret_cast<unsigned long long *>(b.counters + kCntDenseWork), st));
-        BUILD_HIP(launch_exclusive_scan_i32(b.nslots, m, p->slot_base, b.part_m, st));
-        BUILD_HIP(launch_exclusive_scan_i64(b.bsize, m, b.bbase, b.part_m, st));
-        BUILD_HIP(hipMemcpyAsync(hb, b.counters, kCntTotal * sizeof(int64_t), hipMemcpyDeviceToHost, st));
-        BUILD_HIP(hipMemcpyAsync(hb + kHbSlots, p->slot_base + m, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-        BUILD_HIP(hipMemcpyAsync(hb + kHbSlots + 1, b.work_pre + r0, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-        BUILD_HIP(hipMemcpyAsync(hb + kHbSlots + 2, b.bbase + m, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-        BUILD_HIP(hipMemcpyAsync(hb + kHbRange, b.work_pre + r1, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+        BUILD_HIP(launch_scans(ScanJobs().add(b.nslots, m, p->slot_base).add(b.bsize, m, b.bbase), b.part_m, st));
+        BUILD_HIP(launch_read_back(ReadBack()
+                                       .add(b.counters, 0, kCntTotal)
+                                       .add(p->slot_base + m, kHbSlots)
+                                       .add(b.work_pre + r0, kHbSlots + 1)
+                                       .add(b.bbase + m, kHbSlots + 2)
+                                       .add(b.work_pre + r1, kHbRange),
+                                   hb, st));
         BUILD_HIP(hipStreamSynchronize(st));
         for (int c = 0; c < kNumLists; ++c) p->list_count[c] = hb[kCntClass + c];
         p->S = hb[kHbSlots];
@@ -1007,13 +1003,19 @@ slg_status plan_block(slg_plan *p, int64_t r0, int64_t r1) {
     }
     phase2.add(&b.slot_row, p->S);
     phase2.add(&p->bounds, p->nbounds);
-    phase2.add(&p->tickets, kTkTotal);
-    for (int c = 0; c < kLightClasses; ++c) phase2.add(&p->lists[c], p->list_count[c]);
-    for (int h = 0; h < kNumHeavyLists; ++h) phase2.add(&p->heavy[h], p->list_count[kLightClasses + h]);
+    // counters and tier lists side by side (cleared together), in int64 words
     static_assert(sizeof(HeavyDesc) % 8 == 0, "HeavyDesc is filled as int64 words");
+    int64_t at[kNumLists] = {};
+    p->list_words = (kTkTotal + 7) / 8 * 8;
+    for (int c = 0; c < kLightClasses + kNumHeavyLists; ++c) {
+        at[c] = p->list_words;
+        const int64_t bytes = p->list_count[c] * (int64_t)(c < kLightClasses ? sizeof(int32_t) : sizeof(HeavyDesc));
+        p->list_words += (bytes + 63) / 64 * 8;
+    }
+    phase2.add(&p->tickets, p->list_words);
     phase2.add(&p->slot_cnt, (size_t)K * p->S);
     phase2.add(&p->slot_off, (size_t)K * (p->S + 1));
-    phase2.add(&b.part_s, scan_partials_size(p->S));
+    phase2.add(&b.part_s, K * scan_partials_size(p->S));
     {  // the count store, when it fits the context's limit
         const int64_t nh = p->list_count[kLightClasses];
         // below store_min (a batch of small graphs) the store's extra
@@ -1065,6 +1067,9 @@ slg_status plan_block(slg_plan *p, int64_t r0, int64_t r1) {
     }
     for (const auto &a : phase2.items) BUILD_HIP(sc.get(a.first, a.second));
     for (const auto &a : hub_once.items) BUILD_HIP(p->scratch.get(a.first, a.second));
+    for (int c = 0; c < kLightClasses; ++c) p->lists[c] = reinterpret_cast<int32_t *>(p->tickets + at[c]);
+    for (int h = 0; h < kNumHeavyLists; ++h)
+        p->heavy[h] = reinterpret_cast<HeavyDesc *>(p->tickets + at[kLightClasses + h]);
     if (!hub_once.items.empty()) {
         StageTimer tm(ctx, kStSlots, st);
         BUILD_HIP(launch_hub_bits(p->pr.n, b.hub, p->pr.vs_ptr, b.vs_cid, p->kept_rows, b.nib, st));
@@ -1073,9 +1078,6 @@ slg_status plan_block(slg_plan *p, int64_t r0, int64_t r1) {
     p->slots.count = p->S;
     p->slots.row = b.slot_row;
     BUILD_HIP(enqueue_slots_count(p, st));
-    for (int k = 0; k < K; ++k)
-        BUILD_HIP(hipMemcpyAsync(hb + kHbEdges + k, p->slot_off + (size_t)k * (p->S + 1) + p->S, sizeof(int64_t),
-                                 hipMemcpyDeviceToHost, st));
     for (int h = 0; h < 2; ++h)
         BUILD_HIP(launch_heavy_edges(p->heavy[h], p->list_count[kLightClasses + h], p->slot_cnt, p->S, K,
                                      p->tickets + kTkHeavyEdges, st));
@@ -1086,10 +1088,10 @@ slg_status plan_block(slg_plan *p, int64_t r0, int64_t r1) {
                                    st));
     if (p->use_store)
         BUILD_HIP(launch_sum_i32(p->store.n, p->list_count[kLightClasses], p->tickets + kTkStored, st));
-    BUILD_HIP(hipMemcpyAsync(hb + kHbHeavyEdges, p->tickets + kTkHeavyEdges, 6 * sizeof(int64_t),
-                             hipMemcpyDeviceToHost, st));  // heavy edges, stored, dense room, asked, kept, edges
-    BUILD_HIP(hipMemcpyAsync(hb + kHbHeavyEdges + 6, b.counters + kCntErr, sizeof(int64_t),
-                             hipMemcpyDeviceToHost, st));
+    ReadBack rb;  // edges; heavy edges, stored, dense room, asked, kept, edges; the error flag
+    for (int k = 0; k < K; ++k) rb.add(p->slot_off + (size_t)k * (p->S + 1) + p->S, kHbEdges + k);
+    rb.add(p->tickets + kTkHeavyEdges, kHbHeavyEdges, 6).add(b.counters + kCntErr, kHbHeavyEdges + 6);
+    BUILD_HIP(launch_read_back(rb, hb, st));
     BUILD_HIP(hipStreamSynchronize(st));
     if (hb[kHbHeavyEdges + 6] & 0xffffffff)
         return fail(ctx, SLG_ERR_DEVICE, "internal error: a tier list overflowed its planned size");
@@ -1212,7 +1214,6 @@ slg_status emit_range(slg_plan *p, int64_t r0, int64_t r1, int64_t s0, int64_t s
                                           p->slot_off, nullptr, st));
         }
     }
-    SLG_HIP(ctx, launch_fill_i64(p->tickets + kTkEmit, kNumHeavyLists, 0, st));
     // a chunk's heavy slots: a contiguous part of each heavy list (all are
     // in slot order), found on the device and read back
     int64_t lo[kNumHeavyLists] = {}, hi[kNumHeavyLists];
@@ -1227,17 +1228,15 @@ slg_status emit_range(slg_plan *p, int64_t r0, int64_t r1, int64_t s0, int64_t s
         }
     } else if (s0 > 0 || s1 < p->S) {
         int64_t *hb = ctx->pinned + kHbRange;
+        ReadBack rb;
         for (int h = 0; h < kNumHeavyLists; ++h) {
             if (hi[h] <= 0) continue;
             SLG_HIP(ctx, launch_heavy_range(p->heavy[h], hi[h], s0, s1, p->tickets + kTkRange + 2 * h, st));
-            SLG_HIP(ctx, hipMemcpyAsync(hb + 2 * h, p->tickets + kTkRange + 2 * h, 2 * sizeof(int64_t),
-                                        hipMemcpyDeviceToHost, st));
+            rb.add(p->tickets + kTkRange + 2 * h, 2 * h, 2);
         }
-        if (p->hub_rows > 0) {
-            int64_t *hr = hb + 2 * kNumHeavyLists;
-            SLG_HIP(ctx, hipMemcpyAsync(hr, p->b.hub_pre + r0, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-            SLG_HIP(ctx, hipMemcpyAsync(hr + 1, p->b.hub_pre + r1, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-        }
+        if (p->hub_rows > 0)
+            rb.add(p->b.hub_pre + r0, 2 * kNumHeavyLists).add(p->b.hub_pre + r1, 2 * kNumHeavyLists + 1);
+        SLG_HIP(ctx, launch_read_back(rb, hb, st));
         SLG_HIP(ctx, hipStreamSynchronize(st));
         if (p->hub_rows > 0) {
             hub_lo = hb[2 * kNumHeavyLists];
@@ -1249,6 +1248,11 @@ slg_status emit_range(slg_plan *p, int64_t r0, int64_t r1, int64_t s0, int64_t s
                 hi[h] = hb[2 * h + 1];
             }
     }
+    // slots without a store are walked again, from tickets
+    const bool walk[kNumHeavyLists] = {hi[0] > lo[0] && !p->use_store, hi[1] > lo[1],
+                                       hi[2] > lo[2] && (!p->use_dstore || p->dense_stored > p->dense_kept)};
+    if (walk[0] || walk[1] || walk[2])
+        SLG_HIP(ctx, launch_fill_i64(p->tickets + kTkEmit, kNumHeavyLists, 0, st));
     for (int wide = 0; wide < 2; ++wide) {
         const int64_t cnt = hi[wide] - lo[wide];
         if (cnt <= 0) continue;
@@ -1269,7 +1273,7 @@ slg_status emit_range(slg_plan *p, int64_t r0, int64_t r1, int64_t s0, int64_t s
         if (p->use_dstore)
             SLG_HIP(ctx, launch_heavy_store_emit(p->heavy[2] + lo[2], cnt, p->S, part, prm, p->slot_off,
                                                  p->pr.cid_row, st));
-        if (!p->use_dstore || p->dense_stored > p->dense_kept)
+        if (walk[2])
             SLG_HIP(ctx, launch_dense(true, p->heavy[2] + lo[2], cnt, nullptr, p->S, p->bounds, p->pr, prm, nullptr,
                                       p->slot_off, p->tickets + kTkEmit + 2, p->dense_grid,
                                       p->use_dstore ? &part : nullptr, nullptr, 0, st));

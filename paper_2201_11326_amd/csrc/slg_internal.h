@@ -163,7 +163,43 @@ struct LightStore {
     int32_t *n;
 };
 
+// Exclusive prefix sums of up to SLG_MAX_S arrays in one go: out[0..n], the
+// last entry the total.
+struct ScanJob {
+    const void *in;
+    int64_t *out;
+    int64_t n;
+    int64_t bytes;  // of an entry of `in`: 1, 4 or 8
+};
+struct ScanJobs {
+    ScanJob j[SLG_MAX_S];
+    int32_t count = 0;
+    template <typename T>
+    ScanJobs &add(const T *in, int64_t n, int64_t *out) {
+        j[count++] = {in, out, n > 0 ? n : 0, (int64_t)sizeof(T)};
+        return *this;
+    }
+};
+
+// Device int64 values to be copied to host memory: n from src to host[at..].
+struct ReadBack {
+    struct Item {
+        const int64_t *src;
+        int32_t at, n;
+    };
+    Item item[SLG_MAX_S + 8];
+    int32_t count = 0;
+    ReadBack &add(const int64_t *src, int at, int n = 1) {
+        item[count++] = {src, at, n};
+        return *this;
+    }
+};
+
 // ---- launchers (all enqueue on `st`, return hipError_t) -------------------
+// partials: jobs.count * scan_partials_size(the longest n).
+hipError_t launch_scans(const ScanJobs &jobs, int64_t *partials, hipStream_t st);
+// host: pinned memory, valid once the stream has been waited for.
+hipError_t launch_read_back(const ReadBack &rb, int64_t *host, hipStream_t st);
 hipError_t launch_exclusive_scan_i64(const int64_t *in, int64_t n, int64_t *out, int64_t *partials,
                                      hipStream_t st);
 hipError_t launch_exclusive_scan_i32(const int32_t *in, int64_t n, int64_t *out, int64_t *partials,
@@ -204,13 +240,15 @@ hipError_t launch_row_plan(const Pruned &g, int32_t s_min, int32_t light_max, in
                            unsigned long long *class_count, int *err, unsigned long long *heavy_work,
                            unsigned long long *dense_work, int64_t *pieces, unsigned long long *num_pieces,
                            hipStream_t st);
-// Light lists and heavy descriptors (heavy lists in slot order). hat:
-// int64[3 (m + 1)] and hcnt: int32[3 m] scratch, partials: scan_partials_size(m).
+// Light lists and heavy descriptors (heavy lists in slot order). planned: the
+// lists' sizes; caps: their room. hat: int64[3 (m + 1)] and hcnt: int32[3 m]
+// scratch, partials: 3 scan_partials_size(m).
 hipError_t launch_fill_slots(int64_t m, const int64_t *he_ptr, const int64_t *slot_base,
                              const int32_t *nslots, const int32_t *jmax, const uint8_t *rclass,
                              const int64_t *bbase, const int32_t *cid, int64_t *hat, int32_t *hcnt,
                              int64_t *partials, int32_t *slot_row, int32_t *const *lists, HeavyDesc *const *heavy,
-                             const int64_t *caps, unsigned long long *list_fill, int *err, hipStream_t st);
+                             const int64_t *caps, const int64_t *planned, unsigned long long *list_fill, int *err,
+                             hipStream_t st);
 // A row block [r0, r1): nslots / rclass / bsize of the other rows zeroed
 // (from the *_all copies of every row), the block's list sizes and heavy /
 // dense 2-paths added to class_count / heavy_work / dense_work.

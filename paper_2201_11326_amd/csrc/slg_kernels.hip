@@ -41,68 +41,115 @@ namespace {
 // ---------------------------------------------------------------------------
 // device-wide exclusive scan (int64 output, out[n] = total)
 // ---------------------------------------------------------------------------
+// Several arrays per launch, since a small plan is bound by its launches (4 us
+// of host time each): arrays of at most kScanSmall entries by one workgroup
+// each, longer ones in three launches for all of them. With one read-back
+// launch per synchronisation and one clearing of all lists, a plan of 1000
+// rows and six thresholds takes 36 launches instead of 66, 371 -> 164 us. At
+// kScanSmall entries one workgroup takes about as long as three launches.
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
 constexpr int kScanTile = kScanThreads * kScanItems;
+constexpr int kScanSmallThreads = 1024, kScanSmallItems = 8;
+constexpr int64_t kScanSmall = 4 * kScanSmallThreads * kScanSmallItems;
 
-template <typename T>
-__global__ __launch_bounds__(kScanThreads) void scan_reduce_kernel(const T *__restrict__ in,
-                                                                   int64_t n,
-                                                                   int64_t *__restrict__ partials) {
-    __shared__ int64_t ws[kScanThreads / 64];
-    const int64_t base = (int64_t)blockIdx.x * kScanTile;
-    int64_t s = 0;
-    for (int t = threadIdx.x; t < kScanTile; t += kScanThreads) {
-        int64_t idx = base + t;
-        if (idx < n) s += (int64_t)in[idx];
+__device__ __forceinline__ int64_t scan_item(const ScanJob &j, int64_t idx) {
+    if (j.bytes == 1) return as_global(static_cast<const uint8_t *>(j.in))[idx];
+    if (j.bytes == 4) return as_global(static_cast<const int32_t *>(j.in))[idx];
+    return as_global(static_cast<const int64_t *>(j.in))[idx];
+}
+
+__global__ __launch_bounds__(kScanSmallThreads) void scan_small_kernel(ScanJobs jobs) {
+    __shared__ int64_t ws[kScanSmallThreads / 64];
+    const ScanJob j = jobs.j[blockIdx.x];
+    int64_t carry = 0;
+    constexpr int kTile = kScanSmallThreads * kScanSmallItems;
+    for (int64_t t0 = 0; t0 < j.n; t0 += kTile) {
+        const int64_t base = t0 + (int64_t)threadIdx.x * kScanSmallItems;
+        int64_t v[kScanSmallItems], local = 0, tot;
+#pragma unroll
+        for (int r = 0; r < kScanSmallItems; ++r) {
+            v[r] = base + r < j.n ? scan_item(j, base + r) : 0;
+            local += v[r];
+        }
+        int64_t run = carry + block_excl_scan<kScanSmallThreads>(local, ws, tot);
+#pragma unroll
+        for (int r = 0; r < kScanSmallItems; ++r) {
+            if (base + r < j.n) as_global(j.out)[base + r] = run;
+            run += v[r];
+        }
+        carry += tot;
     }
+    if (threadIdx.x == 0) as_global(j.out)[j.n] = carry;
+}
+
+// Job y's partial sums are partials[y * stride, ...).
+__global__ __launch_bounds__(kScanThreads) void scan_reduce_kernel(ScanJobs jobs, int64_t *__restrict__ partials,
+                                                                   int64_t stride) {
+    __shared__ int64_t ws[kScanThreads / 64];
+    const ScanJob j = jobs.j[blockIdx.y];
+    const int64_t base = (int64_t)blockIdx.x * kScanTile;
+    if (base >= j.n) return;
+    int64_t s = 0;
+    for (int t = threadIdx.x; t < kScanTile; t += kScanThreads)
+        if (base + t < j.n) s += scan_item(j, base + t);
     s = wave_sum(s);
     if (lane_id() == 0) ws[threadIdx.x >> 6] = s;
     __syncthreads();
     if (threadIdx.x == 0) {
         int64_t t = 0;
         for (int w = 0; w < kScanThreads / 64; ++w) t += ws[w];
-        partials[blockIdx.x] = t;
+        partials[blockIdx.y * stride + blockIdx.x] = t;
     }
 }
 
-__global__ __launch_bounds__(1024) void scan_top_kernel(int64_t *__restrict__ partials, int64_t nb) {
+__global__ __launch_bounds__(1024) void scan_top_kernel(ScanJobs jobs, int64_t *__restrict__ partials,
+                                                        int64_t stride) {
     __shared__ int64_t ws[16];
+    int64_t *part = partials + blockIdx.x * stride;
+    const int64_t nb = (jobs.j[blockIdx.x].n + kScanTile - 1) / kScanTile;
     int64_t carry = 0;
     for (int64_t base = 0; base < nb; base += 1024) {
         int64_t idx = base + threadIdx.x;
-        int64_t x = idx < nb ? partials[idx] : 0;
+        int64_t x = idx < nb ? part[idx] : 0;
         int64_t tot;
         int64_t ex = block_excl_scan<1024>(x, ws, tot);
-        if (idx < nb) partials[idx] = carry + ex;
+        if (idx < nb) part[idx] = carry + ex;
         carry += tot;
     }
-    if (threadIdx.x == 0) partials[nb] = carry;
+    if (threadIdx.x == 0) part[nb] = carry;
 }
 
-template <typename T>
-__global__ __launch_bounds__(kScanThreads) void scan_down_kernel(const T *__restrict__ in, int64_t n,
-                                                                 const int64_t *__restrict__ partials,
-                                                                 int64_t *__restrict__ out) {
+__global__ __launch_bounds__(kScanThreads) void scan_down_kernel(ScanJobs jobs, const int64_t *__restrict__ partials,
+                                                                 int64_t stride) {
     __shared__ int64_t ws[kScanThreads / 64];
+    const ScanJob j = jobs.j[blockIdx.y];
+    const int64_t nb = (j.n + kScanTile - 1) / kScanTile;
+    const int64_t *part = partials + blockIdx.y * stride;
+    if (blockIdx.x == 0 && threadIdx.x == 0) as_global(j.out)[j.n] = nb > 0 ? part[nb] : 0;
+    if ((int64_t)blockIdx.x >= nb) return;
     const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
     int64_t v[kScanItems];
     int64_t local = 0;
 #pragma unroll
     for (int r = 0; r < kScanItems; ++r) {
-        int64_t idx = base + r;
-        v[r] = idx < n ? (int64_t)in[idx] : 0;
+        v[r] = base + r < j.n ? scan_item(j, base + r) : 0;
         local += v[r];
     }
     int64_t tot;
-    int64_t run = partials[blockIdx.x] + block_excl_scan<kScanThreads>(local, ws, tot);
+    int64_t run = part[blockIdx.x] + block_excl_scan<kScanThreads>(local, ws, tot);
 #pragma unroll
     for (int r = 0; r < kScanItems; ++r) {
-        int64_t idx = base + r;
-        if (idx < n) out[idx] = run;
+        if (base + r < j.n) as_global(j.out)[base + r] = run;
         run += v[r];
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = partials[gridDim.x];
+}
+
+// Values into pinned host memory, one workgroup per entry (a launch instead
+// of a copy per value).
+__global__ void read_back_kernel(ReadBack rb, int64_t *host) {
+    const ReadBack::Item it = rb.item[blockIdx.x];
+    for (int t = threadIdx.x; t < it.n; t += blockDim.x) as_global(host)[it.at + t] = as_global(it.src)[t];
 }
 
 __global__ void fill_i64_kernel(int64_t *__restrict__ p, int64_t n, int64_t value) {
@@ -113,16 +160,6 @@ __global__ void fill_i64_kernel(int64_t *__restrict__ p, int64_t n, int64_t valu
 __global__ void fill_i32_kernel(int32_t *__restrict__ p, int64_t n, int32_t value) {
     int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx < n) p[idx] = value;
-}
-
-template <typename T>
-hipError_t exclusive_scan(const T *in, int64_t n, int64_t *out, int64_t *partials, hipStream_t st) {
-    if (n <= 0) return launch_fill_i64(out, 1, 0, st);
-    const int64_t nb = (n + kScanTile - 1) / kScanTile;
-    scan_reduce_kernel<T><<<dim3((unsigned)nb), dim3(kScanThreads), 0, st>>>(in, n, partials);
-    scan_top_kernel<<<1, 1024, 0, st>>>(partials, nb);
-    scan_down_kernel<T><<<dim3((unsigned)nb), dim3(kScanThreads), 0, st>>>(in, n, partials, out);
-    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -644,13 +681,13 @@ __global__ __launch_bounds__(256) void fill_slots_kernel(
 
 // Heavy slots per row, by class: the prefix sums place every heavy row's
 // descriptors in row order, so each heavy list is in slot order.
+// `lists`: one bit per heavy list that has slots.
 __global__ void heavy_counts_kernel(int64_t m, const uint8_t *__restrict__ rclass, const int32_t *__restrict__ nslots,
-                                    int32_t *__restrict__ cnt) {
+                                    int lists, int32_t *__restrict__ cnt) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) {
         const int c = rclass[i];
-        cnt[i] = c == kHeavy ? nslots[i] : 0;
-        cnt[m + i] = c == kHeavyWide ? nslots[i] : 0;
-        cnt[2 * m + i] = c == kDense ? nslots[i] : 0;
+        for (int h = 0; h < kNumHeavyLists; ++h)
+            if (lists >> h & 1) cnt[(int64_t)h * m + i] = c == kHeavy + h ? nslots[i] : 0;
     }
 }
 
@@ -2782,17 +2819,39 @@ hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t value, hipStream_t st)
     return hipGetLastError();
 }
 
+hipError_t launch_scans(const ScanJobs &jobs, int64_t *partials, hipStream_t st) {
+    if (jobs.count <= 0) return hipSuccess;
+    int64_t n = 0;
+    for (int t = 0; t < jobs.count; ++t) n = jobs.j[t].n > n ? jobs.j[t].n : n;
+    const unsigned count = (unsigned)jobs.count;
+    if (n <= kScanSmall) {
+        scan_small_kernel<<<count, kScanSmallThreads, 0, st>>>(jobs);
+        return hipGetLastError();
+    }
+    const int64_t nb = (n + kScanTile - 1) / kScanTile, stride = scan_partials_size(n);
+    scan_reduce_kernel<<<dim3((unsigned)nb, count), kScanThreads, 0, st>>>(jobs, partials, stride);
+    scan_top_kernel<<<count, 1024, 0, st>>>(jobs, partials, stride);
+    scan_down_kernel<<<dim3((unsigned)nb, count), kScanThreads, 0, st>>>(jobs, partials, stride);
+    return hipGetLastError();
+}
+
 hipError_t launch_exclusive_scan_i64(const int64_t *in, int64_t n, int64_t *out, int64_t *partials,
                                      hipStream_t st) {
-    return exclusive_scan(in, n, out, partials, st);
+    return launch_scans(ScanJobs().add(in, n, out), partials, st);
 }
 hipError_t launch_exclusive_scan_i32(const int32_t *in, int64_t n, int64_t *out, int64_t *partials,
                                      hipStream_t st) {
-    return exclusive_scan(in, n, out, partials, st);
+    return launch_scans(ScanJobs().add(in, n, out), partials, st);
 }
 hipError_t launch_exclusive_scan_u8(const uint8_t *in, int64_t n, int64_t *out, int64_t *partials,
                                     hipStream_t st) {
-    return exclusive_scan(in, n, out, partials, st);
+    return launch_scans(ScanJobs().add(in, n, out), partials, st);
+}
+
+hipError_t launch_read_back(const ReadBack &rb, int64_t *host, hipStream_t st) {
+    if (rb.count <= 0) return hipSuccess;
+    read_back_kernel<<<(unsigned)rb.count, 64, 0, st>>>(rb, host);
+    return hipGetLastError();
 }
 
 hipError_t launch_keep_incidence(int64_t nnz, const int32_t *v_idx, const int64_t *he_ptr, int64_t m,
@@ -2869,7 +2928,8 @@ hipError_t launch_fill_slots(int64_t m, const int64_t *he_ptr, const int64_t *sl
                              const int32_t *nslots, const int32_t *jmax, const uint8_t *rclass,
                              const int64_t *bbase, const int32_t *cid, int64_t *hat, int32_t *hcnt,
                              int64_t *partials, int32_t *slot_row, int32_t *const *lists, HeavyDesc *const *heavy,
-                             const int64_t *caps, unsigned long long *list_fill, int *err, hipStream_t st) {
+                             const int64_t *caps, const int64_t *planned, unsigned long long *list_fill, int *err,
+                             hipStream_t st) {
     if (m <= 0) return hipSuccess;
     LightLists ll;
     for (int c = 0; c < kLightClasses; ++c) ll.l[c] = lists[c];
@@ -2877,11 +2937,16 @@ hipError_t launch_fill_slots(int64_t m, const int64_t *he_ptr, const int64_t *sl
     ll.err = err;
     fill_slots_kernel<<<grid_for(m, 256 * kFillRows), 256, 0, st>>>(m, he_ptr, slot_base, nslots, jmax, rclass,
                                                                      bbase, slot_row, ll, hat, list_fill);
-    heavy_counts_kernel<<<grid_for(m, 256) < 8192 ? grid_for(m, 256) : 8192, 256, 0, st>>>(m, rclass, nslots, hcnt);
-    hipError_t e;
+    int used = 0;
+    for (int h = 0; h < kNumHeavyLists; ++h) used |= planned[kLightClasses + h] > 0 ? 1 << h : 0;
+    if (!used) return hipGetLastError();
+    heavy_counts_kernel<<<grid_for(m, 256) < 8192 ? grid_for(m, 256) : 8192, 256, 0, st>>>(m, rclass, nslots, used,
+                                                                                          hcnt);
+    ScanJobs jobs;
     for (int h = 0; h < kNumHeavyLists; ++h)
-        if ((e = exclusive_scan(hcnt + (int64_t)h * m, m, hat + (int64_t)h * (m + 1), partials, st)) != hipSuccess)
-            return e;
+        if (used >> h & 1) jobs.add(hcnt + (int64_t)h * m, m, hat + (int64_t)h * (m + 1));
+    const hipError_t e = launch_scans(jobs, partials, st);
+    if (e != hipSuccess) return e;
     HeavyLists hl;
     for (int h = 0; h < kNumHeavyLists; ++h) {
         hl.l[h] = heavy[h];
