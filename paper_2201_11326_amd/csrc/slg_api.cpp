@@ -2156,16 +2156,29 @@ slg_status slg_symmetrize(slg_context *ctx, int64_t m, const int64_t *row_ptr, c
     sc.st = st;
     sc.arena = ctx->arena.get();
     int64_t *err = nullptr, *lower_ptr = nullptr;
-    const int32_t *sorted[3] = {};
     SLG_HIP(ctx, sc.get(&err, 1));
     SLG_HIP(ctx, sc.get(&lower_ptr, m + 1));
     SLG_HIP(ctx, launch_fill_i64(err, 1, 0, st));
-    SLG_HIP(ctx, launch_check_upper(row_ptr, row, col, n, m, reinterpret_cast<int *>(err), st));
-    // the upper triangle sorted by column (stable: rows stay ascending),
-    // left in the sort's own buffers
-    SLG_HIP(ctx, sort_pairs(sc, col, row, w, n, bits_for(m), nullptr, nullptr, nullptr, st, sorted));
-    SLG_HIP(ctx, launch_symmetric(sorted[0], sorted[1], sorted[2], row_ptr, row, col, w, n, m, lower_ptr, sym_ptr,
-                                  sym_col, sym_w, st));
+    if (n > 0 && transpose_packs(m)) {
+        TransposeScratch t{};
+        const int64_t counts = transpose_counts_size(n, m);
+        SLG_HIP(ctx, sc.get(&t.hist, counts));
+        SLG_HIP(ctx, sc.get(&t.off, counts + 1));
+        SLG_HIP(ctx, sc.get(&t.partials, scan_partials_size(counts)));
+        SLG_HIP(ctx, sc.get(&t.buckets, 2050));
+        SLG_HIP(ctx, sc.get(&t.key, n));
+        if (w) SLG_HIP(ctx, sc.get(&t.w, n));
+        SLG_HIP(ctx, launch_transpose(row_ptr, row, col, w, n, m, t, lower_ptr, sym_ptr, sym_col, sym_w,
+                                      reinterpret_cast<int *>(err), st));
+    } else {  // more vertices than a packed word can name: the general sort
+        const int32_t *sorted[3] = {};
+        SLG_HIP(ctx, launch_check_upper(row_ptr, row, col, n, m, reinterpret_cast<int *>(err), st));
+        // the upper triangle sorted by column (stable: rows stay ascending),
+        // left in the sort's own buffers
+        SLG_HIP(ctx, sort_pairs(sc, col, row, w, n, bits_for(m), nullptr, nullptr, nullptr, st, sorted));
+        SLG_HIP(ctx, launch_symmetric(sorted[0], sorted[1], sorted[2], row_ptr, row, col, w, n, m, lower_ptr,
+                                      sym_ptr, sym_col, sym_w, st));
+    }
     SLG_HIP(ctx, hipMemcpyAsync(ctx->pinned, err, sizeof(int64_t), hipMemcpyDeviceToHost, st));
     SLG_HIP(ctx, hipStreamSynchronize(st));
     sc.release();

@@ -413,6 +413,21 @@ hipError_t launch_symmetric(const int32_t *skey, const int32_t *srow, const int3
                             int64_t *lower_ptr, int64_t *sym_ptr, int32_t *sym_col, int32_t *sym_w,
                             hipStream_t st);
 
+// The same from the upper triangle alone, checked on the way (err as
+// launch_check_upper), n > 0 and m that transpose_packs: two passes, the
+// second straight into the output. hist, off: transpose_counts_size(n, m) and
+// one more; partials: scan_partials_size of it; buckets: 2050; key, w: n (w
+// null without weights).
+struct TransposeScratch {
+    int32_t *hist, *key, *w;
+    int64_t *off, *partials, *buckets;
+};
+bool transpose_packs(int64_t m);
+int64_t transpose_counts_size(int64_t n, int64_t m);
+hipError_t launch_transpose(const int64_t *row_ptr, const int32_t *row, const int32_t *col, const int32_t *w,
+                            int64_t n, int64_t m, const TransposeScratch &t, int64_t *lower_ptr, int64_t *sym_ptr,
+                            int32_t *sym_col, int32_t *sym_w, int *err, hipStream_t st);
+
 // Preprocessing (slg_prep.hip). key[i] = |e_i| or n - |e_i|, id[i] = i.
 hipError_t launch_size_keys(const int64_t *he_ptr, int64_t m, int64_t n, int descending, int32_t *key, int32_t *id,
                             hipStream_t st);

@@ -7,6 +7,7 @@
 //   - the symmetric CSR of L_s from its upper triangle.
 // Every step is integer work and deterministic: the sort is stable, so the
 // output does not depend on scheduling.
+#include "slg_device.h"
 #include "slg_internal.h"
 
 namespace slg {
@@ -309,6 +310,331 @@ __global__ void sym_upper_kernel(const int32_t *__restrict__ row, const int32_t 
     }
 }
 
+// ---------------------------------------------------------------------------
+// Transpose of an upper triangle into the lower parts of its symmetric CSR
+// ---------------------------------------------------------------------------
+// A stable sort of the edges by column in two passes, high half of the
+// column's bits first. Bound by HBM traffic; the general sort above took four
+// passes over three arrays and a copy into place (16.6 ms for 4.4e8 edges of
+// 200 000 hyperedges, 13.0 of them in its passes and their copy). Here
+//   - the first pass's counts come with the check of the input;
+//   - the first pass writes (row, low half) in one word beside the weight;
+//   - the second pass goes bucket by bucket, so its counts are positions in
+//     the whole list, give the column starts, and its items go straight to
+//     their places in the output.
+// A wavefront ranks kTrRounds rounds of its own contiguous items without a
+// barrier (its counts in LDS, in order), so a tile has eight barriers where the
+// sort above has three per round. The same edges now take 8.9 ms: 2.9 and 2.5
+// in the passes (20 and 16 bytes an edge, 3.0 and 2.8 TB/s), 1.4 in the counts
+// and the check, 2.0 in the upper copy. Tiles of 6144 items (three workgroups
+// a CU) took 4.2 and 3.5, of 16 384 (one) 2.7 and 2.6.
+constexpr int kTrThreads = 512;
+constexpr int kTrWaves = kTrThreads / 64;
+constexpr int kTrRounds = 16;
+constexpr int kTrWaveItems = 64 * kTrRounds;
+constexpr int kTrTile = kTrWaves * kTrWaveItems;
+
+struct TransposeShape {
+    int64_t n, m, chunk, chunks;  // items, vertices; items per chunk (whole tiles), first-pass chunks
+    int low;                      // bits of the second digit
+};
+
+// Bucket b (columns [b << low, (b + 1) << low)): items [beg[b], beg[b + 1])
+// of the first pass's output, second-pass chunks [first[b], first[b + 1]).
+struct TransposeBuckets {
+    int64_t *beg, *first;
+};
+
+template <int NB>
+__device__ __forceinline__ void transpose_counts(const int (&h)[NB], int64_t at, int64_t step,
+                                                 int32_t *__restrict__ hist) {
+    for (int d = threadIdx.x; d < NB; d += kTrThreads) hist[at + d * step] = h[d];
+}
+
+// Checks that (row_ptr, row, col) is the upper triangle of a graph on m
+// vertices in CSR order (row_ptr itself is check_ptr_kernel's): r < col < m,
+// columns strictly increasing along a row, and each run of a row id starts
+// and ends where row_ptr says, which the lanes at its ends look up. And the
+// first pass's counts: hist[d * chunks + chunk] for d = col >> low.
+template <int NB>
+__global__ __launch_bounds__(kTrThreads) void check_count_kernel(TransposeShape s, const int64_t *__restrict__ row_ptr,
+                                                                 const int32_t *__restrict__ row,
+                                                                 const int32_t *__restrict__ col,
+                                                                 int32_t *__restrict__ hist, int *__restrict__ err) {
+    __shared__ int h[NB];
+    const int lane = lane_id();
+    for (int d = threadIdx.x; d < NB; d += kTrThreads) h[d] = 0;
+    __syncthreads();
+    bool bad = false;
+    const int64_t beg = blockIdx.x * s.chunk, end = min(s.n, beg + s.chunk);
+    for (int64_t e0 = beg + threadIdx.x; e0 - lane < end; e0 += kTrThreads * 8) {
+        int32_t r[8], c[8], r0[8], c0[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int64_t e = e0 + j * kTrThreads;
+            r[j] = e < end ? row[e] : 0;
+            c[j] = e < end ? col[e] : 1;
+            r0[j] = c0[j] = -1;
+            if (lane == 0 && e > 0 && e < end) {
+                r0[j] = row[e - 1];
+                c0[j] = col[e - 1];
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int64_t e = e0 + j * kTrThreads;
+            const int ru = __shfl_up(r[j], 1), cu = __shfl_up(c[j], 1);
+            const int rp = lane ? ru : r0[j], cp = lane ? cu : c0[j];
+            // one count per run of equal digits
+            const int d = ((unsigned)c[j] >> s.low) & (NB - 1);
+            const unsigned long long heads = __ballot(lane == 0 || d != (int)(((unsigned)cu >> s.low) & (NB - 1)));
+            const int live = (int)min<int64_t>(64, end - (e - lane));
+            if (e >= end) continue;
+            if (heads >> lane & 1) {
+                const unsigned long long after = lane < 63 ? heads >> (lane + 1) : 0ull;
+                atomicAdd(&h[d], min(live, after ? lane + __ffsll(after) : 64) - lane);
+            }
+            if (r[j] < 0 || c[j] <= r[j] || c[j] >= s.m) {
+                bad = true;
+                continue;
+            }
+            if (rp == r[j]) {
+                bad |= cp >= c[j];
+            } else {
+                bad |= row_ptr[r[j]] != e;
+                if (e > 0) bad |= rp < 0 || rp >= s.m || row_ptr[rp + 1] != e;
+            }
+            if (e == s.n - 1) bad |= row_ptr[r[j] + 1] != s.n;
+        }
+    }
+    if (bad) atomicOr(err, 1);
+    __syncthreads();
+    transpose_counts(h, blockIdx.x, s.chunks, hist);
+}
+
+// One workgroup: the buckets from the first pass's offsets.
+template <int NB>
+__global__ __launch_bounds__(1024) void bucket_kernel(TransposeShape s, const int64_t *__restrict__ off,
+                                                      TransposeBuckets k) {
+    static_assert(NB <= 1024, "one bucket per thread");
+    __shared__ int64_t ws[16];
+    const int b = threadIdx.x;
+    int64_t beg = s.n, q = 0, tot;
+    if (b < NB) {
+        beg = off[b * s.chunks];
+        q = (off[(b + 1) * s.chunks] - beg + s.chunk - 1) / s.chunk;
+    }
+    const int64_t first = block_excl_scan<1024>(q, ws, tot);
+    if (b < NB) {
+        k.beg[b] = beg;
+        k.first[b] = first;
+    }
+    if (b == 0) {
+        k.beg[NB] = s.n;
+        k.first[NB] = tot;
+    }
+}
+
+// The bucket of second-pass chunk g, or -1 past the last; its items are
+// [beg, end), its counts (off-) set at + d * step.
+template <int NB>
+__device__ __forceinline__ int chunk_of(const TransposeShape &s, const TransposeBuckets &k, int64_t g, int64_t &beg,
+                                        int64_t &end, int64_t &at, int64_t &step) {
+    if (g >= k.first[NB]) return -1;
+    int b = 0;
+#pragma unroll
+    for (int w = NB / 2; w > 0; w >>= 1)  // the last bucket whose first chunk is <= g
+        if (k.first[b + w] <= g) b += w;
+    const int64_t f = k.first[b];
+    step = k.first[b + 1] - f;
+    beg = k.beg[b] + (g - f) * s.chunk;
+    end = min(k.beg[b + 1], beg + s.chunk);
+    at = f * NB + (g - f);
+    return b;
+}
+
+template <int NB>
+__global__ __launch_bounds__(kTrThreads) void bucket_count_kernel(TransposeShape s, TransposeBuckets k,
+                                                                  const uint32_t *__restrict__ key,
+                                                                  int32_t *__restrict__ hist) {
+    __shared__ int h[NB];
+    int64_t beg, end, at, step;
+    if (chunk_of<NB>(s, k, blockIdx.x, beg, end, at, step) < 0) return;
+    for (int d = threadIdx.x; d < NB; d += kTrThreads) h[d] = 0;
+    __syncthreads();
+    const unsigned mask = (1u << s.low) - 1u;
+    for (int64_t e0 = beg + threadIdx.x; e0 < end; e0 += kTrThreads * 8) {
+        uint32_t x[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = e0 + j * kTrThreads < end ? key[e0 + j * kTrThreads] : 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (e0 + j * kTrThreads < end) atomicAdd(&h[x[j] & mask], 1);
+    }
+    __syncthreads();
+    transpose_counts(h, at, step, hist);
+}
+
+// lower_ptr[c]: the sorted position of column c's first item, c in [0, m];
+// sym_ptr[c] beside it.
+template <int NB>
+__global__ void column_starts_kernel(TransposeShape s, TransposeBuckets k, const int64_t *__restrict__ off,
+                                     const int64_t *__restrict__ row_ptr, int64_t *__restrict__ lower_ptr,
+                                     int64_t *__restrict__ sym_ptr) {
+    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c <= s.m; c += (int64_t)gridDim.x * blockDim.x) {
+        int64_t p = s.n;
+        if (c < s.m) {
+            const int64_t b = c >> s.low, d = c & ((1 << s.low) - 1), f = k.first[b], q = k.first[b + 1] - f;
+            p = q > 0 ? off[f * NB + d * q] : k.beg[b];
+        }
+        lower_ptr[c] = p;
+        sym_ptr[c] = p + row_ptr[c];
+    }
+}
+
+// One chunk, a tile at a time. FIRST: (col, row, w) to (row << low | low bits
+// of col, w) by the high digit; else (key, w) of one bucket to (row, w) of
+// the output by the low digit.
+template <int NB, bool FIRST>
+__global__ __launch_bounds__(kTrThreads, 4) void transpose_kernel(
+    TransposeShape s, TransposeBuckets k, const int32_t *__restrict__ key_in, const int32_t *__restrict__ row_in,
+    const int32_t *__restrict__ w_in, const int64_t *__restrict__ off, const int64_t *__restrict__ row_ptr,
+    int32_t *__restrict__ key_out, int32_t *__restrict__ w_out) {
+    __shared__ int32_t tile[kTrTile];
+    __shared__ uint16_t dig[kTrTile];
+    __shared__ uint16_t cnt[kTrWaves][NB];  // counts of a wavefront, then its starts within the digit
+    __shared__ int64_t run[NB];             // next output position of a digit
+    __shared__ uint16_t dstart[NB];         // a digit's first place in the tile
+    __shared__ int ws[kTrWaves];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    int64_t beg, end, at, step;
+    int64_t room = s.n;  // of the output
+    if (FIRST) {
+        beg = blockIdx.x * s.chunk;
+        end = min(s.n, beg + s.chunk);
+        at = blockIdx.x;
+        step = s.chunks;
+        for (int d = threadIdx.x; d < NB; d += kTrThreads) run[d] = off[at + d * step];
+    } else {
+        const int b = chunk_of<NB>(s, k, blockIdx.x, beg, end, at, step);
+        if (b < 0) return;
+        room = 2 * s.n;
+        for (int d = threadIdx.x; d < NB; d += kTrThreads) {
+            const int64_t c = ((int64_t)b << s.low) + d;
+            // no items have these digits unless the input check has failed
+            run[d] = d >> s.low || c >= s.m ? room : off[at + d * step] + row_ptr[c];
+        }
+    }
+    const unsigned mask = (1u << s.low) - 1u;
+    for (int64_t t0 = beg; t0 < end; t0 += kTrTile) {
+        const int tn = (int)min((int64_t)kTrTile, end - t0);
+        const int first = wave * kTrWaveItems + lane;
+        uint32_t x[kTrRounds];
+        int32_t y[kTrRounds], wt[kTrRounds];
+        int place[kTrRounds];  // digit << 16 | rank within the wavefront's digit
+#pragma unroll
+        for (int r = 0; r < kTrRounds; ++r) {
+            const int i = first + 64 * r;
+            x[r] = i < tn ? (uint32_t)key_in[t0 + i] : 0u;
+            if (FIRST) y[r] = i < tn ? row_in[t0 + i] : 0;
+        }
+        for (int d = lane; d < NB; d += 64) cnt[wave][d] = 0;
+        volatile uint16_t *mine = cnt[wave];
+        wave_lds_sync();
+#pragma unroll
+        for (int r = 0; r < kTrRounds; ++r) {
+            const bool in = first + 64 * r < tn;  // a prefix of the lanes
+            const int d = FIRST ? (int)((x[r] >> s.low) & (NB - 1)) : (int)(x[r] & mask);
+            x[r] = FIRST ? (uint32_t)y[r] << s.low | (x[r] & mask) : x[r] >> s.low;  // what is written
+            const unsigned long long live = __ballot(in);
+            int rank, num;
+            const int dp = __shfl_up(d, 1);
+            if (FIRST && !__ballot(in && lane > 0 && d < dp)) {
+                // one row's columns ascend: equal digits are runs of lanes
+                const unsigned long long heads = __ballot(in && (lane == 0 || d != dp));
+                const int head = 63 - __clzll(heads & (~0ull >> (63 - lane)) | 1ull);
+                const unsigned long long after = lane < 63 ? heads & (~0ull << (lane + 1)) : 0ull;
+                rank = lane - head;
+                num = (after ? __ffsll(after) - 1 : __popcll(live)) - head;
+            } else {
+                unsigned long long peers = live;
+#pragma unroll
+                for (int bit = 1; bit < NB; bit <<= 1) {
+                    const unsigned long long bb = __ballot(d & bit);
+                    peers &= d & bit ? bb : ~bb;
+                }
+                rank = bits_below(peers);
+                num = __popcll(peers);
+            }
+            const int before = mine[d];
+            place[r] = d << 16 | (before + rank);
+            if (in && rank == 0) mine[d] = (uint16_t)(before + num);
+            wave_lds_sync();
+        }
+#pragma unroll
+        for (int r = 0; r < kTrRounds; ++r) wt[r] = w_in && first + 64 * r < tn ? w_in[t0 + first + 64 * r] : 0;
+        __syncthreads();
+        // counts to starts: of each wavefront within its digit, of the digit in the tile
+        {
+            constexpr int per = NB / kTrThreads > 0 ? NB / kTrThreads : 1;
+            int tot[per], sum = 0;
+#pragma unroll
+            for (int j = 0; j < per; ++j) {
+                const int d = threadIdx.x * per + j;
+                tot[j] = 0;
+                if (d >= NB) break;
+                int run_w = 0;
+#pragma unroll
+                for (int w = 0; w < kTrWaves; ++w) {
+                    const int c = cnt[w][d];
+                    cnt[w][d] = (uint16_t)run_w;
+                    run_w += c;
+                }
+                tot[j] = run_w;
+                sum += run_w;
+            }
+            int all;
+            int st = block_excl_scan<kTrThreads>(sum, ws, all);
+#pragma unroll
+            for (int j = 0; j < per; ++j) {
+                if (threadIdx.x * per + j < NB) dstart[threadIdx.x * per + j] = (uint16_t)st;
+                st += tot[j];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kTrRounds; ++r) {
+            const int d = place[r] >> 16;
+            place[r] = dstart[d] + cnt[wave][d] + (place[r] & 0xFFFF);
+            if (first + 64 * r < tn) {
+                dig[place[r]] = (uint16_t)d;
+                tile[place[r]] = (int32_t)x[r];
+            }
+        }
+        __syncthreads();
+        auto out = [&](int32_t *__restrict__ to) {
+#pragma unroll 4
+            for (int q = threadIdx.x; q < tn; q += kTrThreads) {
+                const int d = dig[q];
+                const int64_t pos = run[d] + (q - dstart[d]);
+                if (pos >= 0 && pos < room) to[pos] = tile[q];
+            }
+        };
+        out(key_out);
+        if (w_in) {
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < kTrRounds; ++r)
+                if (first + 64 * r < tn) tile[place[r]] = wt[r];
+            __syncthreads();
+            out(w_out);
+        }
+        __syncthreads();
+        // next tile: the digits' positions advance
+        for (int d = threadIdx.x; d < NB; d += kTrThreads) run[d] += (d + 1 < NB ? (int)dstart[d + 1] : tn) - dstart[d];
+    }
+}
+
 // Order-independent digest of an edge list: the number of edges, the sum
 // of the overlaps, and the sum mod 2^64 of SplitMix64's output function
 // (Steele, Lea and Flood's mixer as published by Vigna) applied to
@@ -389,6 +715,66 @@ hipError_t launch_digest(const int32_t *row, const int32_t *col, const int32_t *
 
 hipError_t launch_key_bounds(const int32_t *skey, int64_t n, int64_t m, int64_t *lower_ptr, hipStream_t st) {
     key_bounds_kernel<<<sort_grid(m + 1, 256, 4096), 256, 0, st>>>(skey, n, m, lower_ptr);
+    return hipGetLastError();
+}
+
+// The second digit has the larger half of the bits; a packed word holds the
+// row and it.
+bool transpose_packs(int64_t m) { return m <= (int64_t(1) << 20); }
+
+namespace {
+int transpose_low(int64_t m) {
+    int bits = 1;
+    while ((int64_t(1) << bits) < m) ++bits;
+    return (bits + 1) / 2;
+}
+int transpose_bins(int64_t m) { return m <= (int64_t(1) << 18) ? 512 : 1024; }
+// Whole tiles: eight where that leaves at least 1024 chunks.
+int64_t transpose_chunk(int64_t n) {
+    int64_t tiles = n / (int64_t(1024) * kTrTile);
+    tiles = tiles < 1 ? 1 : (tiles > 8 ? 8 : tiles);
+    return tiles * kTrTile;
+}
+}  // namespace
+
+int64_t transpose_counts_size(int64_t n, int64_t m) {
+    const int64_t chunk = transpose_chunk(n);
+    return ((n + chunk - 1) / chunk + transpose_bins(m)) * transpose_bins(m);
+}
+
+hipError_t launch_transpose(const int64_t *row_ptr, const int32_t *row, const int32_t *col, const int32_t *w,
+                            int64_t n, int64_t m, const TransposeScratch &t, int64_t *lower_ptr, int64_t *sym_ptr,
+                            int32_t *sym_col, int32_t *sym_w, int *err, hipStream_t st) {
+    if (n <= 0 || !transpose_packs(m)) return hipErrorInvalidValue;
+    const int64_t chunk = transpose_chunk(n), chunks = (n + chunk - 1) / chunk;
+    const int nb = transpose_bins(m);
+    if (chunks + nb > INT_MAX) return hipErrorInvalidValue;
+    const TransposeShape s{n, m, chunk, chunks, transpose_low(m)};
+    const TransposeBuckets k{t.buckets, t.buckets + 1025};
+    const unsigned g1 = (unsigned)chunks, g2 = (unsigned)(chunks + nb);
+    check_ptr_kernel<<<sort_grid(m, 256, 4096), 256, 0, st>>>(row_ptr, m, n, err);
+    hipError_t e;
+#define SLG_TRANSPOSE(NB)                                                                                            \
+    do {                                                                                                             \
+        check_count_kernel<NB><<<g1, kTrThreads, 0, st>>>(s, row_ptr, row, col, t.hist, err);                        \
+        if ((e = launch_exclusive_scan_i32(t.hist, chunks * NB, t.off, t.partials, st)) != hipSuccess) return e;     \
+        bucket_kernel<NB><<<1, 1024, 0, st>>>(s, t.off, k);                                                          \
+        transpose_kernel<NB, true><<<g1, kTrThreads, 0, st>>>(s, k, col, row, w, t.off, nullptr, t.key, t.w);        \
+        if ((e = launch_fill_i32(t.hist, (chunks + NB) * NB, 0, st)) != hipSuccess) return e;                        \
+        bucket_count_kernel<NB><<<g2, kTrThreads, 0, st>>>(s, k, reinterpret_cast<const uint32_t *>(t.key), t.hist); \
+        if ((e = launch_exclusive_scan_i32(t.hist, (chunks + NB) * NB, t.off, t.partials, st)) != hipSuccess)        \
+            return e;                                                                                                \
+        column_starts_kernel<NB><<<sort_grid(m + 1, 256, 4096), 256, 0, st>>>(s, k, t.off, row_ptr, lower_ptr,       \
+                                                                               sym_ptr);                             \
+        transpose_kernel<NB, false><<<g2, kTrThreads, 0, st>>>(s, k, t.key, nullptr, w ? t.w : nullptr, t.off,       \
+                                                                row_ptr, sym_col, sym_w);                            \
+    } while (0)
+    if (nb == 512)
+        SLG_TRANSPOSE(512);
+    else
+        SLG_TRANSPOSE(1024);
+#undef SLG_TRANSPOSE
+    sym_upper_kernel<<<sort_grid(n, 256 * kFlat, 16384), 256, 0, st>>>(row, col, w, n, m, lower_ptr, sym_col, sym_w);
     return hipGetLastError();
 }
 
