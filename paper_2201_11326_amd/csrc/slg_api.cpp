@@ -39,6 +39,15 @@ enum Work {
     kWkBlocks, kWkTwoPaths, kWkHeavyTwoPaths, kWkDenseTwoPaths, kWkEdges, kWkHeavyEdges, kWkDenseEdges,
     kWkDenseSlots, kWkDenseStored, kWkDenseRewalk, kNumWork
 };
+
+// Heavy 2-paths from which a plan keeps the heavy slots' store by itself: two
+// launches lay it out, and its emit pass is a read (5000 skewed rows: 47 us
+// with the layout, 117 to walk the 2-paths again). Below, a walk is as short.
+constexpr int64_t kStoreMin = int64_t(1) << 16;
+constexpr int64_t kStoreMinBudget = int64_t(1) << 24;  // under a memory budget
+// 2-paths up to which the light rows' store has room for every row's (at most
+// 96 MiB), laid out without a launch of its own.
+constexpr int64_t kWholeStore = int64_t(1) << 24;
 }  // namespace
 
 struct slg_context {
@@ -58,7 +67,9 @@ struct slg_context {
     int32_t dense_ratio = kDenseRatio;  // the dense tier's rule (ratio 0: off)
     int32_t dense_min = kDenseMinRange;
     int64_t store_limit = int64_t(32) << 30;  // largest count store a plan keeps (0: none)
-    int64_t store_min = int64_t(1) << 24;     // fewest heavy 2-paths for which a plan keeps one
+    int64_t store_min = kStoreMin;            // fewest heavy 2-paths for which a plan keeps one
+    int64_t lstore_min = 0;                   // and fewest 2-paths for the light rows' store
+    bool store_set = false;                   // the caller chose them
     int64_t list_shortfall = 0;  // error-path tests: heavy lists planned this much short
     uint64_t budget = 0;
     bool has_alloc = false;
@@ -371,7 +382,7 @@ struct slg_plan {
     int64_t kept_rows = 0;         // |E_{s_min}|
     int64_t *store_work = nullptr; // [heavy slots]: 2-paths per slot
     int64_t store_limit = 0;
-    int64_t store_min = 0;
+    int64_t store_min = 0, lstore_min = 0;
     int64_t list_shortfall = 0;
     int64_t plan_lo = 0, plan_hi = -1;  // rows the rows phase plans (-1: to the last)
     int64_t stored_ranks = 0;
@@ -744,14 +755,13 @@ hipError_t enqueue_slots_count(slg_plan *p, hipStream_t st) {
     if (e != hipSuccess) return e;
     {
         StageTimer tm(ctx, kStCountLight, lst);
-        if (p->use_lstore) {  // the light store's layout
+        if (p->use_lstore && p->lwork) {  // the light store's layout
             if ((e = launch_light_work(m, b.rclass, b.work, p->lwork, lst)) != hipSuccess) return e;
             if ((e = launch_exclusive_scan_i32(p->lwork, m, p->lstore.off, b.part_light, lst)) != hipSuccess) return e;
         }
-        for (int c = 0; c < kLightClasses; ++c)
-            if ((e = launch_light(c, false, p->lists[c], p->list_count[c], p->slots, p->pr, p->prm, p->slot_cnt,
-                                  nullptr, (p->use_lstore && c > 0) ? &p->lstore : nullptr, lst)) != hipSuccess)
-                return e;
+        if ((e = launch_light_count(p->lists, p->list_count, p->slots, p->pr, p->prm, p->slot_cnt,
+                                    p->use_lstore ? &p->lstore : nullptr, lst)) != hipSuccess)
+            return e;
     }
     {
         StageTimer tm(ctx, kStBounds, st);
@@ -1024,16 +1034,25 @@ slg_status plan_block(slg_plan *p, int64_t r0, int64_t r1) {
         p->use_store = nh > 0 && p->store_limit > 0 && bytes <= p->store_limit &&
                        p->heavy_two_paths >= p->store_min;
         // the light rows' pairs: at most their 2-paths (all but the heavy and dense ones)
-        const int64_t lcap = p->two_paths - p->heavy_two_paths - p->dense_two_paths;
-        const int64_t lbytes = lcap * 6 + m * 16 + 16;
-        p->use_lstore = p->store_limit > 0 && lcap > 0 && p->two_paths >= p->store_min &&
+        // a small plan of all rows lays them out by the 2-paths of every row,
+        // whose prefix it has
+        const bool whole = r0 == 0 && r1 == m && p->two_paths < kWholeStore;
+        const int64_t lrows = p->two_paths - p->heavy_two_paths - p->dense_two_paths;
+        const int64_t lcap = whole ? p->two_paths : lrows;
+        const int64_t lbytes = lcap * 6 + m * (whole ? 4 : 16) + 16;
+        p->use_lstore = p->store_limit > 0 && lrows > 0 && p->two_paths >= p->lstore_min &&
                         (p->use_store ? bytes : 0) + lbytes <= p->store_limit;
+        p->lwork = nullptr;
         if (p->use_lstore) {
             phase2.add(&p->lstore.key, lcap);
             phase2.add(&p->lstore.cnt, lcap);
-            phase2.add(&p->lstore.off, m + 1);
             phase2.add(&p->lstore.n, m);
-            phase2.add(&p->lwork, m);
+            if (whole) {
+                p->lstore.off = b.work_pre;
+            } else {
+                phase2.add(&p->lstore.off, m + 1);
+                phase2.add(&p->lwork, m);
+            }
         }
         if (p->use_store) {
             phase2.add(&p->store.ent, p->heavy_two_paths);
@@ -1143,6 +1162,7 @@ slg_plan *plan_new(slg_context *ctx, slg_graph *g, const int32_t *s, int32_t num
     p->dense_grid = ctx->dense_resident;
     p->store_limit = ctx->store_limit;
     p->store_min = ctx->store_min;
+    p->lstore_min = ctx->lstore_min;
     p->list_shortfall = ctx->list_shortfall;
     return p;
 }
@@ -1205,14 +1225,12 @@ slg_status emit_range(slg_plan *p, int64_t r0, int64_t r1, int64_t s0, int64_t s
     }
     {
         StageTimer tm(ctx, kStEmitLight, st);
-        for (int c = 0; c < kLightClasses; ++c) {
-            if (p->use_lstore && c > 0)
-                SLG_HIP(ctx, launch_light_store_emit(p->lists[c], p->list_count[c], p->slots, p->lstore, prm,
-                                                     p->slot_off, st));
-            else
+        if (p->use_lstore)
+            SLG_HIP(ctx, launch_light_store_emit(p->lists, p->list_count, p->slots, p->lstore, prm, p->slot_off, st));
+        else
+            for (int c = 0; c < kLightClasses; ++c)
                 SLG_HIP(ctx, launch_light(c, true, p->lists[c], p->list_count[c], p->slots, p->pr, prm, nullptr,
                                           p->slot_off, nullptr, st));
-        }
     }
     // a chunk's heavy slots: a contiguous part of each heavy list (all are
     // in slot order), found on the device and read back
@@ -1693,7 +1711,8 @@ slg_status slg_context_set_count_store(slg_context *ctx, int64_t max_bytes, int6
     if (max_bytes < 0 || min_two_paths < 0)
         return fail(ctx, SLG_ERR_INVALID_ARG, "max_bytes and min_two_paths must be >= 0");
     ctx->store_limit = max_bytes;
-    ctx->store_min = min_two_paths;
+    ctx->store_min = ctx->lstore_min = min_two_paths;
+    ctx->store_set = true;
     return SLG_OK;
 }
 
@@ -1968,12 +1987,15 @@ slg_status set_error(slg_context *ctx, slg_status code, const char *msg) { retur
 
 void share_arena(slg_context *ctx, const std::shared_ptr<Arena> &arena) { ctx->arena = arena; }
 
-void copy_tuning(slg_context *dst, const slg_context *src) {
+void copy_tuning(slg_context *dst, const slg_context *src, bool budget) {
     dst->light_max = src->light_max;
     dst->slot_work = src->slot_work;
     dst->heavy_grid = src->heavy_grid;
     dst->store_limit = src->store_limit;
     dst->store_min = src->store_min;
+    dst->lstore_min = src->lstore_min;
+    dst->store_set = src->store_set;
+    if (budget && !src->store_set) dst->store_min = dst->lstore_min = kStoreMinBudget;
     dst->dense_ratio = src->dense_ratio;
     dst->dense_min = src->dense_min;
 }

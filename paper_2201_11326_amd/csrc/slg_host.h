@@ -64,7 +64,7 @@ slg_status set_error(slg_context *ctx, slg_status code, const char *msg);
 slg_status create_context(int device, uint64_t mem_budget_bytes, const slg_allocator *alloc, bool second_stream,
                           slg_context **out);
 // Copies the plan-shape tuning (slg_context_set_tuning) of `src` to `dst`.
-void copy_tuning(slg_context *dst, const slg_context *src);
+void copy_tuning(slg_context *dst, const slg_context *src, bool budget);
 // Makes `ctx` take its scratch and outputs from `arena` (shared by a
 // server's slots).
 void share_arena(slg_context *ctx, const std::shared_ptr<Arena> &arena);

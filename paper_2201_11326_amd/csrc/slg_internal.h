@@ -153,9 +153,9 @@ struct CountStore {
     int32_t *n;
 };
 
-// The same for the light rows (wavefront-sort tier): row i holds n[i]
-// (partner id, overlap) pairs in partner order at off[i], the exclusive
-// prefix of the light rows' 2-path counts.
+// The same for the light rows: row i holds n[i] (partner id, overlap) pairs
+// in partner order at off[i], an exclusive prefix of the light (or of all)
+// rows' 2-path counts.
 struct LightStore {
     int32_t *key;
     uint16_t *cnt;
@@ -266,16 +266,19 @@ hipError_t launch_heavy_range(const HeavyDesc *desc, int64_t count, int64_t s0, 
 hipError_t launch_bounds(const Pruned &g, const HeavyDesc *desc, int64_t count, int32_t *bounds,
                          hipStream_t st);
 
-// K3/K4/K5: count (EMIT=false) or emit (EMIT=true) per slot.
-// store (counting pass of the wavefront-sort classes only, or null): keep
-// the overlaps.
+// K3/K4/K5: count (EMIT=false) or emit (EMIT=true) per slot of one class.
+// store (counting pass only, or null): keep the overlaps.
 hipError_t launch_light(int cls, bool emit, const int32_t *list, int64_t count, const Slots &sl,
                         const Pruned &g, const EmitParams &ep, int64_t *slot_cnt,
                         const int64_t *slot_off, const LightStore *store, hipStream_t st);
-// Emit pass of a wavefront-sort class list from the light store.
-hipError_t launch_light_store_emit(const int32_t *list, int64_t count, const Slots &sl, const LightStore &store,
-                                   const EmitParams &ep, const int64_t *slot_off, hipStream_t st);
-// lw[i] = 2-paths of row i if it is in a wavefront-sort class, else 0.
+// The counting pass of all light classes.
+hipError_t launch_light_count(const int32_t *const *lists, const int64_t *counts, const Slots &sl, const Pruned &g,
+                              const EmitParams &ep, int64_t *slot_cnt, const LightStore *store, hipStream_t st);
+// Emit pass of all light classes from the light store.
+hipError_t launch_light_store_emit(const int32_t *const *lists, const int64_t *counts, const Slots &sl,
+                                   const LightStore &store, const EmitParams &ep, const int64_t *slot_off,
+                                   hipStream_t st);
+// lw[i] = 2-paths of row i if it is in a light class, else 0.
 hipError_t launch_light_work(int64_t m, const uint8_t *rclass, const int64_t *work, int32_t *lw, hipStream_t st);
 // Persistent launch: `resident` workgroups (0 = a default) take slots from
 // the device counter `ticket`, which the caller zeroes before the launch.

@@ -59,26 +59,50 @@ __device__ __forceinline__ int64_t scan_item(const ScanJob &j, int64_t idx) {
     return as_global(static_cast<const int64_t *>(j.in))[idx];
 }
 
+// Tiles pass through LDS, so that loads and stores are whole lines and a
+// thread still sums neighbours, and the next tile is loaded before this one
+// is summed: 32 768 entries in 26 us without either.
 __global__ __launch_bounds__(kScanSmallThreads) void scan_small_kernel(ScanJobs jobs) {
+    constexpr int kTile = kScanSmallThreads * kScanSmallItems;
     __shared__ int64_t ws[kScanSmallThreads / 64];
+    __shared__ int64_t buf[kTile + kTile / kScanSmallItems];  // an item of padding per thread
+    auto at = [](int i) { return i + i / kScanSmallItems; };
     const ScanJob j = jobs.j[blockIdx.x];
     int64_t carry = 0;
-    constexpr int kTile = kScanSmallThreads * kScanSmallItems;
-    for (int64_t t0 = 0; t0 < j.n; t0 += kTile) {
-        const int64_t base = t0 + (int64_t)threadIdx.x * kScanSmallItems;
-        int64_t v[kScanSmallItems], local = 0, tot;
+    int64_t v[kScanSmallItems];
+    auto load = [&](int64_t t0) {
 #pragma unroll
         for (int r = 0; r < kScanSmallItems; ++r) {
-            v[r] = base + r < j.n ? scan_item(j, base + r) : 0;
-            local += v[r];
+            const int64_t i = t0 + r * kScanSmallThreads + threadIdx.x;
+            v[r] = i < j.n ? scan_item(j, i) : 0;
+        }
+    };
+    load(0);
+    for (int64_t t0 = 0; t0 < j.n; t0 += kTile) {
+#pragma unroll
+        for (int r = 0; r < kScanSmallItems; ++r) buf[at(r * kScanSmallThreads + threadIdx.x)] = v[r];
+        load(t0 + kTile);
+        __syncthreads();
+        int64_t x[kScanSmallItems], local = 0, tot;
+#pragma unroll
+        for (int r = 0; r < kScanSmallItems; ++r) {
+            x[r] = buf[at(threadIdx.x * kScanSmallItems + r)];
+            local += x[r];
         }
         int64_t run = carry + block_excl_scan<kScanSmallThreads>(local, ws, tot);
+        carry += tot;
 #pragma unroll
         for (int r = 0; r < kScanSmallItems; ++r) {
-            if (base + r < j.n) as_global(j.out)[base + r] = run;
-            run += v[r];
+            buf[at(threadIdx.x * kScanSmallItems + r)] = run;
+            run += x[r];
         }
-        carry += tot;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kScanSmallItems; ++r) {
+            const int64_t i = t0 + r * kScanSmallThreads + threadIdx.x;
+            if (i < j.n) as_global(j.out)[i] = buf[at(r * kScanSmallThreads + threadIdx.x)];
+        }
+        __syncthreads();
     }
     if (threadIdx.x == 0) as_global(j.out)[j.n] = carry;
 }
@@ -644,34 +668,36 @@ __global__ __launch_bounds__(256) void fill_slots_kernel(
     if (tid < kNumLists) cursor[tid] = 0;
     __syncthreads();
     // entries per light list: one per row (heavy descriptors are placed by
-    // heavy_desc_kernel, in slot order)
+    // heavy_desc_kernel, in slot order), counted with ballots (with sums over
+    // the wavefront the 1000 rows of a small graph took 13.5 us)
     for (int c = kLight0; c < kLight0 + kLightClasses; ++c) {
-        int mine = 0;
+        int tot = 0;
 #pragma unroll
-        for (int r = 0; r < kFillRows; ++r)
-            if (cls[r] == c) mine += 1;
-        const int tot = wave_sum(mine);
+        for (int r = 0; r < kFillRows; ++r) tot += __popcll(__ballot(cls[r] == c));
         if (lane == 0 && tot) atomicAdd(&cursor[c - 1], (unsigned long long)tot);
     }
     __syncthreads();
     if (tid < kNumLists && cursor[tid]) cursor[tid] = atomicAdd(&list_fill[tid], cursor[tid]);
     __syncthreads();
+    for (int c = kLight0; c < kLight0 + kLightClasses; ++c) {
+        unsigned long long mask[kFillRows], at = 0;
+        int tot = 0;
 #pragma unroll
-    for (int r = 0; r < kFillRows; ++r) {
-        const int64_t i = i0 + r * 256 + tid;
-        for (int c = kLight0; c < kLight0 + kLightClasses; ++c) {
-            const int w = (cls[r] == c) ? 1 : 0;
-            const int incl = wave_incl_scan(w);
-            const int tot = __shfl(incl, 63);
-            if (!tot) continue;
-            unsigned long long at = 0;
-            if (lane == 63) at = atomicAdd(&cursor[c - 1], (unsigned long long)tot);
-            at = __shfl(at, 63);
-            if (!w) continue;
-            const unsigned long long pos = at + incl - w;
+        for (int r = 0; r < kFillRows; ++r) {
+            mask[r] = __ballot(cls[r] == c);
+            tot += __popcll(mask[r]);
+        }
+        if (!tot) continue;
+        if (lane == 0) at = atomicAdd(&cursor[c - 1], (unsigned long long)tot);
+        at = __shfl(at, 0);
+#pragma unroll
+        for (int r = 0; r < kFillRows; ++r) {
+            const unsigned long long pos = at + bits_below(mask[r]);
+            at += __popcll(mask[r]);
+            if (cls[r] != c) continue;
             if (pos < (unsigned long long)ll.cap[c - 1]) {
                 ll.l[c - 1][pos] = (int32_t)base[r];
-                slot_row[base[r]] = (int32_t)i;
+                slot_row[base[r]] = (int32_t)(i0 + r * 256 + tid);
             } else {
                 atomicOr(ll.err, 16);
             }
@@ -737,15 +763,15 @@ __global__ __launch_bounds__(256) void heavy_desc_kernel(
     const int32_t *__restrict__ nslots, const int32_t *__restrict__ jmax,
     const uint8_t *__restrict__ rclass, const int64_t *__restrict__ bbase,
     const int64_t *__restrict__ hat, int32_t *__restrict__ slot_row, HeavyLists hl,
-    const int32_t *__restrict__ cid, int *__restrict__ err) {
+    const int32_t *__restrict__ cid, int rows, int *__restrict__ err) {
     const int lane = lane_id();
     const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x / 64);
-    // 64 rows per wavefront: each lane loads its own row's values, then the
+    // `rows` rows per wavefront: each lane loads its own row's values, then the
     // heavy rows among them are written one after another (a wavefront per
     // row spent 0.43 ms on the classes of 8.8e6 rows)
-    for (int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 64 * 64; i0 < m; i0 += nwaves * 64) {
+    for (int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 64 * rows; i0 < m; i0 += nwaves * rows) {
         const int64_t own = i0 + lane;
-        const int own_cls = own < m ? rclass[own] : kNone;
+        const int own_cls = lane < rows && own < m ? rclass[own] : kNone;
         const bool heavy = own_cls >= kHeavy && own_cls != kDenseHub;
         int own_ns = 0, own_k = 0, own_range = 0, own_w0 = 0, own_base = 0;
         int64_t own_at = 0, own_bb = 0;
@@ -838,21 +864,14 @@ __device__ __forceinline__ void wave_bitonic(int (&key)[KPL], int lane) {
 // its row's partners (the tails of its members' vertex lists), sorts them
 // with a fixed 8-key network in registers, and writes the runs that reach
 // each threshold to its own slot's place in the output.
-template <bool EMIT>
-__global__ __launch_bounds__(256) void tiny_kernel(const int32_t *__restrict__ list, int64_t count, Slots sl,
-                                                   Pruned g, EmitParams prm, int64_t *__restrict__ slot_cnt,
-                                                   const int64_t *__restrict__ slot_off) {
+using TinyKeys = int32_t[kTinyMax][256];  // column per thread: conflict-free
+
+template <bool EMIT, bool STORE>
+__device__ __forceinline__ void tiny_row(int slot, const Slots &sl, const Pruned &g, const EmitParams *ep,
+                                         TinyKeys &keys, int64_t *__restrict__ slot_cnt,
+                                         const int64_t *__restrict__ slot_off, const LightStore &ls) {
     static_assert(kTinyMax == 8, "8-key sorting network");
-    __shared__ int32_t keys[kTinyMax][256];  // column per thread: conflict-free
-    __shared__ EmitParams sp;
-    stage_params(&sp, prm);
-    __syncthreads();
-    const EmitParams *ep = &sp;
     const int tid = threadIdx.x;
-    const int64_t t = (int64_t)blockIdx.x * 256 + tid;
-    if (t >= count) return;
-    const int slot = list[t];
-    if (EMIT && (slot < ep->slot_lo || slot >= ep->slot_hi)) return;  // outside the emitted chunk
     const int i = sl.row[slot];
     const int64_t p0 = g.he_ptr[i], p1 = g.he_ptr[i + 1];
     int n = 0;
@@ -886,6 +905,18 @@ __global__ __launch_bounds__(256) void tiny_kernel(const int32_t *__restrict__ l
         }
         c[r] = run;  // 0 for non-heads
     }
+    if (STORE) {
+        const int64_t base = as_global(ls.off)[i];
+        int at = 0;
+#pragma unroll
+        for (int r = 0; r < kTinyMax; ++r)
+            if (c[r] > 0) {
+                as_global(ls.key)[base + at] = k[r];
+                as_global(ls.cnt)[base + at] = (uint16_t)c[r];
+                ++at;
+            }
+        as_global(ls.n)[i] = at;
+    }
     const int K = ep->k;
     const int64_t S = sl.count;
     const int id0 = ep->row_base ? as_global(ep->row_base)[i] : 0;  // caller's id of row i is i - id0
@@ -912,29 +943,39 @@ __global__ __launch_bounds__(256) void tiny_kernel(const int32_t *__restrict__ l
     }
 }
 
+template <bool EMIT, bool STORE>
+__global__ __launch_bounds__(256) void tiny_kernel(const int32_t *__restrict__ list, int64_t count, Slots sl,
+                                                   Pruned g, EmitParams prm, int64_t *__restrict__ slot_cnt,
+                                                   const int64_t *__restrict__ slot_off, LightStore ls) {
+    __shared__ TinyKeys keys;
+    __shared__ EmitParams sp;
+    stage_params(&sp, prm);
+    __syncthreads();
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= count) return;
+    const int slot = list[t];
+    if (EMIT && (slot < sp.slot_lo || slot >= sp.slot_hi)) return;  // outside the emitted chunk
+    tiny_row<EMIT, STORE>(slot, sl, g, &sp, keys, slot_cnt, slot_off, ls);
+}
+
+// A wavefront's scratch for one row: its partners, and a batch of members'
+// tails (start, flattened start).
+template <int KPL>
+struct LightSmem {
+    int32_t buf[4][64 * KPL];
+    int32_t seg_a[4][64];
+    int32_t seg_p[4][65];
+};
+
 // STORE (counting pass): the row's partners and overlaps are also written
 // to the light store, in partner order.
 template <int KPL, bool EMIT, bool STORE>
-__global__ __launch_bounds__(256) void light_kernel(const int32_t *__restrict__ list, int64_t count,
-                                                    Slots sl, Pruned g, EmitParams prm,
-                                                    int64_t *__restrict__ slot_cnt,
-                                                    const int64_t *__restrict__ slot_off, LightStore ls) {
+__device__ __forceinline__ void light_row(int slot, const Slots &sl, const Pruned &g, const EmitParams *ep,
+                                          int32_t *kb, int32_t *sa, int32_t *sp0, int64_t *__restrict__ slot_cnt,
+                                          const int64_t *__restrict__ slot_off, const LightStore &ls) {
     static_assert(!(STORE && EMIT), "the store is written by the counting pass");
     constexpr int P = 64 * KPL;
-    __shared__ int32_t buf[4][P];
-    __shared__ int32_t seg_a[4][64];
-    __shared__ int32_t seg_p[4][65];
-    __shared__ EmitParams sp;  // thresholds and outputs, indexed by a uniform k
-    stage_params(&sp, prm);
-    __syncthreads();
-    const EmitParams *ep = &sp;
     const int lane = lane_id();
-    const int wv = threadIdx.x >> 6;
-    const int64_t wid = (int64_t)blockIdx.x * 4 + wv;
-    if (wid >= count) return;
-    int32_t *kb = buf[wv];
-    const int slot = list[wid];
-    if (EMIT && (slot < ep->slot_lo || slot >= ep->slot_hi)) return;  // outside the emitted chunk
     const int i = sl.row[slot];
     const int64_t p0 = g.he_ptr[i], p1 = g.he_ptr[i + 1];
 
@@ -942,8 +983,6 @@ __global__ __launch_bounds__(256) void light_kernel(const int32_t *__restrict__ 
     // are taken 64 at a time; their tails are flattened and every lane finds
     // the tail of each of its positions by binary search, so all loads of a
     // batch are independent and coalesced within a tail
-    int32_t *sa = seg_a[wv];
-    int32_t *sp0 = seg_p[wv];
     int w = 0;
     for (int64_t q = p0; q < p1; q += 64) {
         const int64_t p = q + lane;
@@ -1056,6 +1095,72 @@ __global__ __launch_bounds__(256) void light_kernel(const int32_t *__restrict__ 
     }
 }
 
+template <int KPL, bool EMIT, bool STORE>
+__global__ __launch_bounds__(256) void light_kernel(const int32_t *__restrict__ list, int64_t count,
+                                                    Slots sl, Pruned g, EmitParams prm,
+                                                    int64_t *__restrict__ slot_cnt,
+                                                    const int64_t *__restrict__ slot_off, LightStore ls) {
+    __shared__ LightSmem<KPL> sm;
+    __shared__ EmitParams sp;  // thresholds and outputs, indexed by a uniform k
+    stage_params(&sp, prm);
+    __syncthreads();
+    const int wv = threadIdx.x >> 6;
+    const int64_t wid = (int64_t)blockIdx.x * 4 + wv;
+    if (wid >= count) return;
+    const int slot = list[wid];
+    if (EMIT && (slot < sp.slot_lo || slot >= sp.slot_hi)) return;  // outside the emitted chunk
+    light_row<KPL, EMIT, STORE>(slot, sl, g, &sp, sm.buf[wv], sm.seg_a[wv], sm.seg_p[wv], slot_cnt, slot_off, ls);
+}
+
+// The light lists of one launch, the class with the longest rows first:
+// workgroup b takes rows of the last class whose first workgroup is <= b.
+struct LightRuns {
+    const int32_t *list[kLightClasses];
+    int64_t count[kLightClasses];
+    unsigned first[kLightClasses];  // of class kLightClasses - 1, ..., 0
+    __device__ __forceinline__ int class_of(unsigned block, int64_t &group) const {
+        int at = 0;
+#pragma unroll
+        for (int r = 1; r < kLightClasses; ++r) at = first[r] <= block ? r : at;
+        group = block - first[at];
+        return kLightClasses - 1 - at;
+    }
+};
+
+// Counting pass of all light classes in one launch: in a small graph each
+// class has too few rows for the chip and takes as long as its longest row,
+// one class after another (5000 skewed rows: 185 us by class, 93 together).
+template <bool STORE>
+__global__ __launch_bounds__(256) void light_count_kernel(LightRuns runs, Slots sl, Pruned g, EmitParams prm,
+                                                          int64_t *__restrict__ slot_cnt, LightStore ls) {
+    static_assert(kLightClasses == 7, "one case per class");
+    __shared__ union {
+        LightSmem<32> rows;
+        TinyKeys tiny;
+    } sm;
+    __shared__ EmitParams sp;
+    stage_params(&sp, prm);
+    __syncthreads();
+    int64_t group;
+    const int cls = runs.class_of(blockIdx.x, group), wv = threadIdx.x >> 6;
+    const int64_t t = cls ? group * 4 + wv : group * 256 + threadIdx.x;
+    if (t >= runs.count[cls]) return;
+    const int slot = as_global(runs.list[cls])[t];
+#define SLG_ROW(KPL)                                                                                               \
+    light_row<KPL, false, STORE>(slot, sl, g, &sp, sm.rows.buf[wv], sm.rows.seg_a[wv], sm.rows.seg_p[wv], slot_cnt, \
+                                 nullptr, ls)
+    switch (cls) {
+        case 0: tiny_row<false, STORE>(slot, sl, g, &sp, sm.tiny, slot_cnt, nullptr, ls); break;
+        case 1: SLG_ROW(1); break;
+        case 2: SLG_ROW(2); break;
+        case 3: SLG_ROW(4); break;
+        case 4: SLG_ROW(8); break;
+        case 5: SLG_ROW(16); break;
+        default: SLG_ROW(32); break;
+    }
+#undef SLG_ROW
+}
+
 // ---------------------------------------------------------------------------
 // K3-K5 heavy tier: one workgroup per slot, LDS bitmap + rank counters
 // ---------------------------------------------------------------------------
@@ -1063,20 +1168,53 @@ constexpr int kHW = kHeavyThreads / 64;              // wavefronts per heavy wor
 constexpr int kSuperWords = 1024;                    // words per rank superblock (32768 bits)
 constexpr int kSupers = kRangeWords / kSuperWords;
 
-// Emit pass of a wavefront-sort class from the light store: one wavefront
-// per row reads its (partner, overlap) pairs in partner order and compacts
-// every threshold's survivors with ballots.
-__global__ __launch_bounds__(256) void light_store_emit_kernel(const int32_t *__restrict__ list, int64_t count,
-                                                               Slots sl, LightStore ls, EmitParams prm,
+// Emit pass of all light classes from the light store: one wavefront per row
+// (one lane per tiny row) reads its (partner, overlap) pairs in partner order
+// and compacts every threshold's survivors with ballots (8.8e6 small rows:
+// 232 us where gathering and sorting them again took 980).
+__device__ __forceinline__ void tiny_store_row(int slot, const Slots &sl, const LightStore &ls, const EmitParams &sp,
+                                               const int64_t *__restrict__ slot_off) {
+    const int i = sl.row[slot];
+    const int n = min(as_global(ls.n)[i], kTinyMax);
+    const int64_t off = as_global(ls.off)[i];
+    int key[kTinyMax], c[kTinyMax];
+#pragma unroll
+    for (int r = 0; r < kTinyMax; ++r) {
+        key[r] = r < n ? as_global(ls.key)[off + r] : 0;
+        c[r] = r < n ? (int)as_global(ls.cnt)[off + r] : 0;
+    }
+    const int id0 = sp.row_base ? as_global(sp.row_base)[i] : 0;
+    const int srow = sp.row_s ? as_global(sp.row_s)[i] : 0;
+    for (int kk = 0; kk < sp.k; ++kk) {
+        const int sk = sp.row_s ? srow : sp.s[kk];
+        int64_t pos = slot_off[(int64_t)kk * (sl.count + 1) + slot] - sp.out_base[kk];
+#pragma unroll
+        for (int r = 0; r < kTinyMax; ++r)
+            if (c[r] >= sk) {
+                as_global(sp.col[kk])[pos] = key[r] - id0;
+                as_global(sp.w[kk])[pos] = c[r];
+                if (sp.row[kk]) as_global(sp.row[kk])[pos] = i - id0;
+                ++pos;
+            }
+    }
+}
+
+__global__ __launch_bounds__(256) void light_store_emit_kernel(LightRuns runs, Slots sl, LightStore ls, EmitParams prm,
                                                                const int64_t *__restrict__ slot_off) {
     __shared__ EmitParams sp;
     stage_params(&sp, prm);
     __syncthreads();
     const int lane = lane_id();
-    const int64_t wid = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (wid >= count) return;
-    const int slot = list[wid];
+    int64_t group;
+    const int cls = runs.class_of(blockIdx.x, group);
+    const int64_t t = cls ? group * 4 + (threadIdx.x >> 6) : group * 256 + threadIdx.x;
+    if (t >= runs.count[cls]) return;
+    const int slot = as_global(runs.list[cls])[t];
     if (slot < prm.slot_lo || slot >= prm.slot_hi) return;  // outside the emitted chunk
+    if (cls == 0) {
+        tiny_store_row(slot, sl, ls, sp, slot_off);
+        return;
+    }
     const int i = sl.row[slot];
     const int n = as_global(ls.n)[i];
     const int64_t off = as_global(ls.off)[i];
@@ -1117,7 +1255,7 @@ __global__ void light_work_kernel(int64_t m, const uint8_t *__restrict__ rclass,
                                   int32_t *__restrict__ lw) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) {
         const int c = rclass[i];
-        lw[i] = (c > kLight0 && c < kLight0 + kLightClasses) ? (int32_t)work[i] : 0;
+        lw[i] = (c >= kLight0 && c < kLight0 + kLightClasses) ? (int32_t)work[i] : 0;
     }
 }
 
@@ -2952,8 +3090,11 @@ hipError_t launch_fill_slots(int64_t m, const int64_t *he_ptr, const int64_t *sl
         hl.l[h] = heavy[h];
         hl.cap[h] = caps[kLightClasses + h];
     }
-    heavy_desc_kernel<<<wave_grid((m + 63) / 64, 4, 8192), 256, 0, st>>>(m, he_ptr, slot_base, nslots, jmax, rclass,
-                                                              bbase, hat, slot_row, hl, cid, err);
+    // fewer rows per wavefront where 64 would leave most of the chip idle
+    // (37 us on 5000 rows, most of them heavy; 8 us with 8)
+    const int rows = m < (1 << 17) ? 8 : 64;
+    heavy_desc_kernel<<<wave_grid((m + rows - 1) / rows, 4, 8192), 256, 0, st>>>(
+        m, he_ptr, slot_base, nslots, jmax, rclass, bbase, hat, slot_row, hl, cid, rows, err);
     return hipGetLastError();
 }
 
@@ -2981,6 +3122,47 @@ hipError_t launch_heavy_range(const HeavyDesc *desc, int64_t count, int64_t s0, 
     return hipGetLastError();
 }
 
+namespace {
+// All light classes from one launch: `grid` workgroups, runs.first set.
+LightRuns light_runs(const int32_t *const *lists, const int64_t *counts, unsigned &grid) {
+    LightRuns runs{};
+    grid = 0;
+    for (int r = 0; r < kLightClasses; ++r) {
+        const int c = kLightClasses - 1 - r;
+        runs.list[c] = lists[c];
+        runs.count[c] = counts[c];
+        runs.first[r] = grid;
+        grid += counts[c] > 0 ? grid_for(counts[c], c ? 4 : 256) : 0;
+    }
+    return runs;
+}
+
+// Rows of the sorting classes up to which they are counted in one launch. It
+// has the registers and LDS of its largest class, four wavefronts a SIMD:
+// beyond four rows for each the classes' own launches are as fast.
+constexpr int64_t kLightTogether = 16384;
+}  // namespace
+
+hipError_t launch_light_count(const int32_t *const *lists, const int64_t *counts, const Slots &sl, const Pruned &g,
+                              const EmitParams &ep, int64_t *slot_cnt, const LightStore *store, hipStream_t st) {
+    int64_t rows = 0;
+    for (int c = 1; c < kLightClasses; ++c) rows += counts[c];
+    if (rows > kLightTogether || rows == 0) {
+        for (int c = 0; c < kLightClasses; ++c) {
+            const hipError_t e = launch_light(c, false, lists[c], counts[c], sl, g, ep, slot_cnt, nullptr, store, st);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
+    unsigned grid;
+    const LightRuns runs = light_runs(lists, counts, grid);
+    if (store)
+        light_count_kernel<true><<<grid, 256, 0, st>>>(runs, sl, g, ep, slot_cnt, *store);
+    else
+        light_count_kernel<false><<<grid, 256, 0, st>>>(runs, sl, g, ep, slot_cnt, LightStore{});
+    return hipGetLastError();
+}
+
 hipError_t launch_light(int cls, bool emit, const int32_t *list, int64_t count, const Slots &sl,
                         const Pruned &g, const EmitParams &ep, int64_t *slot_cnt,
                         const int64_t *slot_off, const LightStore *store, hipStream_t st) {
@@ -2988,9 +3170,14 @@ hipError_t launch_light(int cls, bool emit, const int32_t *list, int64_t count, 
     if (store && emit) return hipErrorInvalidValue;
     if (cls == 0) {  // one lane per row
         if (emit)
-            tiny_kernel<true><<<grid_for(count, 256), 256, 0, st>>>(list, count, sl, g, ep, slot_cnt, slot_off);
+            tiny_kernel<true, false><<<grid_for(count, 256), 256, 0, st>>>(list, count, sl, g, ep, slot_cnt, slot_off,
+                                                                           LightStore{});
+        else if (store)
+            tiny_kernel<false, true><<<grid_for(count, 256), 256, 0, st>>>(list, count, sl, g, ep, slot_cnt, slot_off,
+                                                                           *store);
         else
-            tiny_kernel<false><<<grid_for(count, 256), 256, 0, st>>>(list, count, sl, g, ep, slot_cnt, slot_off);
+            tiny_kernel<false, false><<<grid_for(count, 256), 256, 0, st>>>(list, count, sl, g, ep, slot_cnt, slot_off,
+                                                                            LightStore{});
         return hipGetLastError();
     }
     const unsigned grid = grid_for(count, 4);
@@ -3020,10 +3207,13 @@ hipError_t launch_light(int cls, bool emit, const int32_t *list, int64_t count, 
     return hipGetLastError();
 }
 
-hipError_t launch_light_store_emit(const int32_t *list, int64_t count, const Slots &sl, const LightStore &store,
-                                   const EmitParams &ep, const int64_t *slot_off, hipStream_t st) {
-    if (count <= 0) return hipSuccess;
-    light_store_emit_kernel<<<grid_for(count, 4), 256, 0, st>>>(list, count, sl, store, ep, slot_off);
+hipError_t launch_light_store_emit(const int32_t *const *lists, const int64_t *counts, const Slots &sl,
+                                   const LightStore &store, const EmitParams &ep, const int64_t *slot_off,
+                                   hipStream_t st) {
+    unsigned grid;
+    const LightRuns runs = light_runs(lists, counts, grid);
+    if (!grid) return hipSuccess;
+    light_store_emit_kernel<<<grid, 256, 0, st>>>(runs, sl, store, ep, slot_off);
     return hipGetLastError();
 }
 

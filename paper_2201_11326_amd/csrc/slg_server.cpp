@@ -230,7 +230,7 @@ slg_status slg_server_create(slg_context *ctx, int32_t workers, uint64_t mem_bud
     for (Worker &w : sv->workers) {
         if (slg::create_context(sv->device, 0, nullptr, false, &w.ctx) != SLG_OK)
             return undo(SLG_ERR_DEVICE, "worker context creation failed");
-        slg::copy_tuning(w.ctx, ctx);
+        slg::copy_tuning(w.ctx, ctx, mem_budget_bytes > 0);
         slg::share_arena(w.ctx, arena);
         if (hipStreamCreateWithFlags(&w.st, hipStreamNonBlocking) != hipSuccess)
             return undo(SLG_ERR_DEVICE, "worker stream creation failed");
