@@ -307,8 +307,8 @@ int bits_for(int64_t values) {  // bits of the largest value below `values`
 
 // Device buffers of a plan, kept so the planning launches can be replayed.
 struct PlanBufs {
-    uint8_t *flag = nullptr;
-    int64_t *pos = nullptr, *part_nnz = nullptr, *vs_ptr = nullptr;
+    KeepBits krow{}, kinc{};     // hyperedges and incidences that pruning keeps
+    int64_t *part_keep = nullptr, *vs_ptr = nullptr;
     int32_t *vs_idx = nullptr;
     int32_t *tail_beg = nullptr, *tail_end = nullptr, *jmax = nullptr, *nslots = nullptr, *slot_row = nullptr;
     int64_t *work = nullptr, *work_pre = nullptr, *counters = nullptr, *part_m = nullptr, *part_light = nullptr;
@@ -319,9 +319,8 @@ struct PlanBufs {
     int32_t *nslots_all = nullptr;  // row blocks: every row's slots, class and boundary
     uint8_t *rclass_all = nullptr;  // entries, kept while each block masks the
     int64_t *bsize_all = nullptr;   // others out
-    uint8_t *keep = nullptr;     // E_s positions (dense tier): kept-row flags,
-    int64_t *kpre = nullptr;     // their exclusive scan,
-    int32_t *cid = nullptr, *cid_row = nullptr, *vs_cid = nullptr;  // ranks, rows of ranks, lists in ranks
+    int32_t *cid = nullptr, *cid_row = nullptr, *vs_cid = nullptr;  // E_s positions (dense tier): ranks, rows of
+                                                                    // ranks, lists in ranks
     uint16_t *vs_win = nullptr;  // the lists' ranks modulo the dense window
     HubInfo *hub = nullptr;      // hub tier: the choice and its histogram,
     int64_t *hub_hist = nullptr;
@@ -628,23 +627,23 @@ hipError_t enqueue_rows(slg_plan *p, hipStream_t st) {
     PlanBufs &b = p->b;
     hipError_t e;
     if ((e = launch_fill_i64(b.counters, p->hubs ? kCntHubHist + hub_hist_words() : kCntRoom, 0, st)) != hipSuccess) return e;
-    if (p->prune) {
+    if (p->prune || p->dense) {
         StageTimer tm(ctx, kStPrune, st);
-        if ((e = launch_keep_incidence(nnz, inc.v_idx, inc.he_ptr, m, p->s_min, p->pr.row_s, b.flag, st)) !=
-            hipSuccess)
-            return e;
-        if ((e = launch_exclusive_scan_u8(b.flag, nnz, b.pos, b.part_nnz, st)) != hipSuccess) return e;
-        if ((e = launch_compact_vertex_lists(n, nnz, inc.v_ptr, inc.v_idx, b.flag, b.pos, b.vs_ptr, b.vs_idx,
-                                             st)) != hipSuccess)
+        if ((e = launch_row_bits(m, inc.he_ptr, p->s_min, p->pr.row_s, b.krow, st)) != hipSuccess) return e;
+        if (p->prune && (e = launch_keep_incidence(nnz, inc.v_idx, m, b.krow, b.kinc, st)) != hipSuccess) return e;
+        ScanJobs jobs;
+        if (p->prune) jobs.add(b.kinc.count, keep_words(nnz), b.kinc.pre);
+        if (p->dense) jobs.add(b.krow.count, keep_words(m), b.krow.pre);
+        if ((e = launch_scans(jobs, b.part_keep, st)) != hipSuccess) return e;
+        if (p->prune && (e = launch_compact_vertex_lists(n, nnz, inc.v_ptr, inc.v_idx, b.kinc, b.vs_ptr, b.vs_idx,
+                                                         st)) != hipSuccess)
             return e;
     }
     if (p->dense) {  // E_s positions: ranks of the kept rows, and the pruned lists in ranks
         StageTimer tm(ctx, kStPrune, st);
-        if ((e = launch_row_keep(m, inc.he_ptr, p->s_min, p->pr.row_s, b.keep, st)) != hipSuccess) return e;
-        if ((e = launch_exclusive_scan_u8(b.keep, m, b.kpre, b.part_m, st)) != hipSuccess) return e;
-        if ((e = launch_cid(m, b.keep, b.kpre, b.cid, b.cid_row, st)) != hipSuccess) return e;
+        if ((e = launch_cid(m, b.krow, b.cid, b.cid_row, st)) != hipSuccess) return e;
         if ((e = launch_vs_cid(n, m, nnz, p->pr.vs_ptr, p->pr.vs_idx, b.cid, b.vs_cid, b.vs_win, st)) != hipSuccess) return e;
-        if (p->hubs && (e = launch_hub_select(n, p->pr.vs_ptr, b.kpre + m, b.hub, b.hub_hist, st)) != hipSuccess)
+        if (p->hubs && (e = launch_hub_select(n, p->pr.vs_ptr, b.krow.pre + keep_words(m), b.hub, b.hub_hist, st)) != hipSuccess)
             return e;
     }
     {
@@ -868,10 +867,15 @@ slg_status plan_rows(slg_plan *p) {
     // (a row has at most m - 1 candidates)
     p->dense = p->dense_ratio > 0 && !pr.row_s && nnz > 0 && m > p->dense_min;
     AllocList phase1;
+    if (p->prune || p->dense) {
+        phase1.add(&b.krow.bits, keep_words(m));
+        phase1.add(&b.krow.count, keep_words(m));
+        phase1.add(&b.part_keep, 2 * scan_partials_size(keep_words(std::max(nnz, m))));
+    }
     if (p->prune) {
-        phase1.add(&b.flag, nnz);
-        phase1.add(&b.pos, nnz + 1);
-        phase1.add(&b.part_nnz, scan_partials_size(nnz));
+        phase1.add(&b.kinc.bits, keep_words(nnz));
+        phase1.add(&b.kinc.count, keep_words(nnz));
+        phase1.add(&b.kinc.pre, keep_words(nnz) + 1);
         phase1.add(&b.vs_ptr, n + 1);
         phase1.add(&b.vs_idx, nnz);
     }
@@ -887,8 +891,7 @@ slg_status plan_rows(slg_plan *p) {
     phase1.add(&b.hat, kNumHeavyLists * (m + 1));
     phase1.add(&b.hcnt, kNumHeavyLists * m);
     if (p->dense) {
-        phase1.add(&b.keep, m);
-        phase1.add(&b.kpre, m + 1);
+        phase1.add(&b.krow.pre, keep_words(m) + 1);
         phase1.add(&b.cid, m);
         phase1.add(&b.cid_row, m);
         phase1.add(&b.vs_cid, nnz + kDensePad);
@@ -938,7 +941,7 @@ slg_status plan_rows(slg_plan *p) {
     ReadBack rb;
     rb.add(b.counters, 0, kCntTotal).add(p->slot_base + m, kHbSlots).add(b.work_pre + m, kHbSlots + 1);
     rb.add(b.bbase + m, kHbSlots + 2);
-    if (p->dense) rb.add(b.kpre + m, kHbRange + 1);
+    if (p->dense) rb.add(b.krow.pre + keep_words(m), kHbRange + 1);
     BUILD_HIP(launch_read_back(rb, hb, st));
     BUILD_HIP(hipStreamSynchronize(st));
     p->kept_rows = p->dense ? hb[kHbRange + 1] : 0;

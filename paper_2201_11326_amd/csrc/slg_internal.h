@@ -163,6 +163,16 @@ struct LightStore {
     int32_t *n;
 };
 
+// What pruning keeps of i = 0..n-1: bit i % 64 of bits[i / 64], the bits set
+// in each word and, at the end, in all before it. The last word may be empty,
+// so that i = n has a place.
+struct KeepBits {
+    unsigned long long *bits;  // keep_words(n)
+    uint8_t *count;            // keep_words(n)
+    int64_t *pre;              // keep_words(n) + 1
+};
+__host__ __device__ inline int64_t keep_words(int64_t n) { return n / 64 + 1; }
+
 // Exclusive prefix sums of up to SLG_MAX_S arrays in one go: out[0..n], the
 // last entry the total.
 struct ScanJob {
@@ -210,21 +220,19 @@ int64_t scan_partials_size(int64_t n);
 // Capacity of the large-row piece list of row planning.
 int64_t plan_pieces_cap(int64_t nnz);
 
-// K1: keep flags per incidence of the vertex CSR, then compaction.
-hipError_t launch_keep_incidence(int64_t nnz, const int32_t *v_idx, const int64_t *he_ptr, int64_t m,
-                                 int32_t s_min, const int32_t *row_s, uint8_t *flag, hipStream_t st);
-hipError_t launch_compact_vertex_lists(int64_t n, int64_t nnz, const int64_t *v_ptr,
-                                       const int32_t *v_idx, const uint8_t *flag,
-                                       const int64_t *pos, int64_t *vs_ptr, int32_t *vs_idx,
-                                       hipStream_t st);
-
-// E_s positions: flag[i] = row i kept at s_min (or its own threshold), pre =
-// its exclusive scan (int64[m+1]), then cid / cid_row, and vs_cid and vs_win
-// over the pruned lists (vs_ptr[n] entries).
-hipError_t launch_row_keep(int64_t m, const int64_t *he_ptr, int32_t s_min, const int32_t *row_s, uint8_t *flag,
+// K1: one bit per hyperedge kept at s_min (or its own threshold row_s), one
+// per incidence of the vertex CSR that names a kept one; then, with `pre` the
+// exclusive prefix sums of `count` (launch_scans), the compaction.
+hipError_t launch_row_bits(int64_t m, const int64_t *he_ptr, int32_t s_min, const int32_t *row_s, const KeepBits &rows,
                            hipStream_t st);
-hipError_t launch_cid(int64_t m, const uint8_t *flag, const int64_t *pre, int32_t *cid, int32_t *cid_row,
-                      hipStream_t st);
+hipError_t launch_keep_incidence(int64_t nnz, const int32_t *v_idx, int64_t m, const KeepBits &rows,
+                                 const KeepBits &inc, hipStream_t st);
+hipError_t launch_compact_vertex_lists(int64_t n, int64_t nnz, const int64_t *v_ptr, const int32_t *v_idx,
+                                       const KeepBits &inc, int64_t *vs_ptr, int32_t *vs_idx, hipStream_t st);
+
+// E_s positions: cid / cid_row from the rows' bits and their prefix sums, and
+// vs_cid and vs_win over the pruned lists (vs_ptr[n] entries).
+hipError_t launch_cid(int64_t m, const KeepBits &rows, int32_t *cid, int32_t *cid_row, hipStream_t st);
 hipError_t launch_vs_cid(int64_t n, int64_t m, int64_t nnz, const int64_t *vs_ptr, const int32_t *vs_idx,
                          const int32_t *cid, int32_t *vs_cid, uint16_t *vs_win, hipStream_t st);
 
