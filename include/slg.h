@@ -321,8 +321,9 @@ slg_status slg_batch_destroy(slg_batch *b);
  * least min_two_paths 2-paths (below that, the store's extra launches cost
  * more than they save; the light rows' overlaps are kept likewise, 6 bytes
  * per 2-path). max_bytes = 0 turns it off. Defaults: 32 GiB and, until this
- * is called, the sizes from which the stores save time, or 2^24 in a server
- * with a memory budget. Results are identical either way. Applies to plans created
+ * is called, the sizes from which the stores save time (a server whose memory
+ * budget has no room for one plans the query again without those below 2^24).
+ * Results are identical either way. Applies to plans created
  * afterwards (and to a server's slots when set before slg_server_create).
  */
 slg_status slg_context_set_count_store(slg_context *ctx, int64_t max_bytes, int64_t min_two_paths);

@@ -44,7 +44,8 @@ enum Work {
 // launches lay it out, and its emit pass is a read (5000 skewed rows: 47 us
 // with the layout, 117 to walk the 2-paths again). Below, a walk is as short.
 constexpr int64_t kStoreMin = int64_t(1) << 16;
-constexpr int64_t kStoreMinBudget = int64_t(1) << 24;  // under a memory budget
+// ... and where the memory budget of a server has no room for smaller ones.
+constexpr int64_t kStoreMinLean = int64_t(1) << 24;
 // 2-paths up to which the light rows' store has room for every row's (at most
 // 96 MiB), laid out without a launch of its own.
 constexpr int64_t kWholeStore = int64_t(1) << 24;
@@ -392,6 +393,7 @@ struct slg_plan {
     int64_t num_edges[SLG_MAX_S] = {};
     const slg::ReserveFn *reserve = nullptr;  // asked before each planning allocation phase
     uint64_t reserved = 0;                    // bytes granted by `reserve`
+    bool *optional = nullptr;                 // set where a store is kept that a lean plan leaves out
 };
 
 struct slg_batch {
@@ -1046,6 +1048,9 @@ slg_status plan_block(slg_plan *p, int64_t r0, int64_t r1) {
         p->use_lstore = p->store_limit > 0 && lrows > 0 && p->two_paths >= p->lstore_min &&
                         (p->use_store ? bytes : 0) + lbytes <= p->store_limit;
         p->lwork = nullptr;
+        if (p->optional && ((p->use_store && p->heavy_two_paths < kStoreMinLean) ||
+                            (p->use_lstore && p->two_paths < kStoreMinLean)))
+            *p->optional = true;
         if (p->use_lstore) {
             phase2.add(&p->lstore.key, lcap);
             phase2.add(&p->lstore.cnt, lcap);
@@ -1990,7 +1995,7 @@ slg_status set_error(slg_context *ctx, slg_status code, const char *msg) { retur
 
 void share_arena(slg_context *ctx, const std::shared_ptr<Arena> &arena) { ctx->arena = arena; }
 
-void copy_tuning(slg_context *dst, const slg_context *src, bool budget) {
+void copy_tuning(slg_context *dst, const slg_context *src) {
     dst->light_max = src->light_max;
     dst->slot_work = src->slot_work;
     dst->heavy_grid = src->heavy_grid;
@@ -1998,14 +2003,13 @@ void copy_tuning(slg_context *dst, const slg_context *src, bool budget) {
     dst->store_min = src->store_min;
     dst->lstore_min = src->lstore_min;
     dst->store_set = src->store_set;
-    if (budget && !src->store_set) dst->store_min = dst->lstore_min = kStoreMinBudget;
     dst->dense_ratio = src->dense_ratio;
     dst->dense_min = src->dense_min;
 }
 
 slg_status serve_query(slg_context *wctx, slg_graph *g, const int32_t *s, int32_t num_s, hipStream_t st,
                        const ReserveFn &reserve, const std::shared_ptr<ServeCore> &core, slg_result **out,
-                       uint64_t *scratch_bytes, uint64_t *output_bytes) {
+                       uint64_t *scratch_bytes, uint64_t *output_bytes, bool lean, bool *optional) {
     *out = nullptr;
     *scratch_bytes = 0;
     *output_bytes = 0;
@@ -2014,6 +2018,10 @@ slg_status serve_query(slg_context *wctx, slg_graph *g, const int32_t *s, int32_
     slg_plan *p = plan_new(wctx, g, s, num_s, st);
     if (!p) return fail(wctx, SLG_ERR_OUT_OF_MEMORY, "host allocation failed");
     p->reserve = &reserve;
+    if (!wctx->store_set) {
+        if (lean) p->store_min = p->lstore_min = kStoreMinLean;
+        p->optional = lean ? nullptr : optional;
+    }
     slg_status rc = plan_build(p);
     *scratch_bytes = p->reserved;
     if (rc != SLG_OK) {

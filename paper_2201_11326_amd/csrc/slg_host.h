@@ -47,10 +47,12 @@ using ReserveFn = std::function<bool(uint64_t bytes)>;
 // *output_bytes what the result holds. A refused reservation ends the query
 // with SLG_ERR_OUT_OF_MEMORY. Any error leaves nothing allocated; the
 // reservations granted so far are reported in *scratch_bytes /
-// *output_bytes for the caller to give back.
+// *output_bytes for the caller to give back. lean: without the stores that
+// small plans keep by themselves; else *optional is set before the first
+// reservation that holds one.
 slg_status serve_query(slg_context *wctx, slg_graph *g, const int32_t *s, int32_t num_s, hipStream_t st,
                        const ReserveFn &reserve, const std::shared_ptr<ServeCore> &core, slg_result **out,
-                       uint64_t *scratch_bytes, uint64_t *output_bytes);
+                       uint64_t *scratch_bytes, uint64_t *output_bytes, bool lean, bool *optional);
 
 // Device of a context / a registered graph's context.
 int context_device(const slg_context *ctx);
@@ -64,7 +66,7 @@ slg_status set_error(slg_context *ctx, slg_status code, const char *msg);
 slg_status create_context(int device, uint64_t mem_budget_bytes, const slg_allocator *alloc, bool second_stream,
                           slg_context **out);
 // Copies the plan-shape tuning (slg_context_set_tuning) of `src` to `dst`.
-void copy_tuning(slg_context *dst, const slg_context *src, bool budget);
+void copy_tuning(slg_context *dst, const slg_context *src);
 // Makes `ctx` take its scratch and outputs from `arena` (shared by a
 // server's slots).
 void share_arena(slg_context *ctx, const std::shared_ptr<Arena> &arena);

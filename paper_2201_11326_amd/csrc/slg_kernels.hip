@@ -50,8 +50,8 @@ namespace {
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
 constexpr int kScanTile = kScanThreads * kScanItems;
-constexpr int kScanSmallThreads = 1024, kScanSmallItems = 8;
-constexpr int64_t kScanSmall = 4 * kScanSmallThreads * kScanSmallItems;
+constexpr int kScanSmallThreads = 512, kScanSmallItems = 8;
+constexpr int64_t kScanSmall = 8 * kScanSmallThreads * kScanSmallItems;
 
 __device__ __forceinline__ int64_t scan_item(const ScanJob &j, int64_t idx) {
     if (j.bytes == 1) return as_global(static_cast<const uint8_t *>(j.in))[idx];
@@ -61,7 +61,9 @@ __device__ __forceinline__ int64_t scan_item(const ScanJob &j, int64_t idx) {
 
 // Tiles pass through LDS, so that loads and stores are whole lines and a
 // thread still sums neighbours, and the next tile is loaded before this one
-// is summed: 32 768 entries in 26 us without either.
+// is summed: 32 768 entries in 26 us without either. (Workgroups of 1024
+// threads and twice the LDS waited for a free CU where several streams are
+// busy: 29 us a scan on 5000 rows instead of FIGURE.)
 __global__ __launch_bounds__(kScanSmallThreads) void scan_small_kernel(ScanJobs jobs) {
     constexpr int kTile = kScanSmallThreads * kScanSmallItems;
     __shared__ int64_t ws[kScanSmallThreads / 64];

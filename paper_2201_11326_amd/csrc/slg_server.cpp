@@ -34,6 +34,7 @@ struct Request {
     int64_t two_paths = 0;
     uint64_t held = 0;  // budget bytes this query holds while it runs
     int32_t attempts = 0;
+    bool lean = false;  // planned without the stores that small plans keep by themselves
 };
 
 struct Worker {
@@ -66,9 +67,15 @@ namespace {
 // Budget request of query q (runs on q's worker thread, inside a planning
 // phase). Returns false to refuse; *yield tells whether q should go back to
 // the queue (another query already waits) rather than fail.
-bool grant(slg_server *sv, Request *q, uint64_t bytes, bool *yield) {
+// optional: the query could do with less; rather than wait it is refused and
+// runs again without (q->lean).
+bool grant(slg_server *sv, Request *q, uint64_t bytes, bool *yield, bool optional) {
     slg::ServeCore &c = *sv->core;
     std::unique_lock<std::mutex> lk(c.mu);
+    if (optional && c.budget && c.used + bytes > c.budget) {
+        q->lean = true;
+        return false;
+    }
     if (c.budget && q->held + bytes > c.budget) return false;  // can never fit
     while (c.budget && c.used + bytes > c.budget) {
         if (sv->stop) {
@@ -121,12 +128,13 @@ void worker_main(slg_server *sv, int wi) {
         ++sv->running;
         lk.unlock();
 
-        bool yield = false;
-        const slg::ReserveFn reserve = [&](uint64_t bytes) { return grant(sv, q, bytes, &yield); };
+        bool yield = false, optional = false;
+        const bool lean = q->lean;
+        const slg::ReserveFn reserve = [&](uint64_t bytes) { return grant(sv, q, bytes, &yield, optional); };
         slg_result *r = nullptr;
         uint64_t scratch = 0, output = 0;
         const slg_status rc = slg::serve_query(w.ctx, q->g, q->s, q->k, w.st, reserve, sv->core, &r, &scratch,
-                                               &output);
+                                               &output, lean, &optional);
         lk.lock();
         --sv->running;
         // the query's stream has drained: its scratch is free again
@@ -142,8 +150,8 @@ void worker_main(slg_server *sv, int wi) {
         } else {
             c.used -= output;
             q->held -= output;
-            if (yield && !sv->stop) {
-                ++sv->yields;
+            if ((yield || q->lean != lean) && !sv->stop) {
+                if (yield) ++sv->yields;
                 sv->queue.push_front(q);
             } else {
                 q->message = q->cancelled ? "server shut down" : slg_last_error(w.ctx);
@@ -230,7 +238,7 @@ slg_status slg_server_create(slg_context *ctx, int32_t workers, uint64_t mem_bud
     for (Worker &w : sv->workers) {
         if (slg::create_context(sv->device, 0, nullptr, false, &w.ctx) != SLG_OK)
             return undo(SLG_ERR_DEVICE, "worker context creation failed");
-        slg::copy_tuning(w.ctx, ctx, mem_budget_bytes > 0);
+        slg::copy_tuning(w.ctx, ctx);
         slg::share_arena(w.ctx, arena);
         if (hipStreamCreateWithFlags(&w.st, hipStreamNonBlocking) != hipSuccess)
             return undo(SLG_ERR_DEVICE, "worker stream creation failed");
