@@ -63,7 +63,7 @@ __device__ __forceinline__ int64_t scan_item(const ScanJob &j, int64_t idx) {
 // thread still sums neighbours, and the next tile is loaded before this one
 // is summed: 32 768 entries in 26 us without either. (Workgroups of 1024
 // threads and twice the LDS waited for a free CU where several streams are
-// busy: 29 us a scan on 5000 rows instead of FIGURE.)
+// busy: 29 us a scan beside seven other queries, now 19.)
 __global__ __launch_bounds__(kScanSmallThreads) void scan_small_kernel(ScanJobs jobs) {
     constexpr int kTile = kScanSmallThreads * kScanSmallItems;
     __shared__ int64_t ws[kScanSmallThreads / 64];
@@ -1045,20 +1045,18 @@ __device__ __forceinline__ void light_row(int slot, const Slots &sl, const Prune
         if (lane == 0) sp0[64] = tot;
         wave_lds_sync();
         for (int fb = 0; fb < tot; fb += 256) {
-            int jr[4];
+            // largest u with sp0[u] <= f, the four positions in lockstep
+            int jr[4], u[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int f = min(fb + lane + 64 * r, tot - 1);
-                int lo = 0, hi = 63;  // largest u with sp0[u] <= f
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (sp0[mid] <= f)
-                        lo = mid;
-                    else
-                        hi = mid - 1;
-                }
-                jr[r] = g.vs_idx[sa[lo] + (f - sp0[lo])];
-            }
+            for (int r = 0; r < 4; ++r) u[r] = 0;
+#pragma unroll
+            for (int step = 32; step > 0; step >>= 1)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (sp0[u[r] + step] <= min(fb + lane + 64 * r, tot - 1)) u[r] += step;
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                jr[r] = g.vs_idx[sa[u[r]] + (min(fb + lane + 64 * r, tot - 1) - sp0[u[r]])];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int f = fb + lane + 64 * r;
@@ -1084,19 +1082,21 @@ __device__ __forceinline__ void light_row(int slot, const Slots &sl, const Prune
     for (int r = 0; r < KPL; ++r) kb[lane * KPL + r] = key[r];
     wave_lds_sync();
 
-    // run-length count: the head of each run of equal j holds the overlap
+    // run-length count: the head of each run of equal j holds the overlap,
+    // its distance to the next head (from the last element down, by ballots:
+    // walking each run took as long as the longest; 5000 skewed rows 94 us so
+    // and with the searches above one after another, 55 now)
     int x[KPL], c[KPL];
+    int next = w;  // the first head after row r
 #pragma unroll
-    for (int r = 0; r < KPL; ++r) {
+    for (int r = KPL - 1; r >= 0; --r) {
         const int e = r * 64 + lane;
         x[r] = e < w ? kb[e] : INT_MAX;
         const bool head = e < w && (e == 0 || kb[e - 1] != x[r]);
-        int n = 0;
-        if (head) {
-            n = 1;
-            while (e + n < w && kb[e + n] == x[r]) ++n;
-        }
-        c[r] = n;  // 0 for non-heads
+        const unsigned long long heads = __ballot(head);
+        const unsigned long long after = lane < 63 ? heads >> (lane + 1) : 0ull;
+        c[r] = head ? (after ? __ffsll(after) : next - e) : 0;  // 0 for non-heads
+        if (heads) next = r * 64 + __ffsll(heads) - 1;
     }
 
     if (STORE) {  // every run head, in partner order
