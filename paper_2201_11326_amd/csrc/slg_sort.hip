@@ -310,6 +310,42 @@ __global__ void sym_upper_kernel(const int32_t *__restrict__ row, const int32_t 
     }
 }
 
+// The same by rows, one workgroup per row, where rows are long: the row's id
+// is not read, and every wavefront's writes but a row's first and last are
+// whole lines, past the caches.
+__global__ __launch_bounds__(256) void sym_upper_rows_kernel(const int64_t *__restrict__ row_ptr,
+                                                             const int32_t *__restrict__ col,
+                                                             const int32_t *__restrict__ w, int64_t n,
+                                                             const int64_t *__restrict__ lower_ptr,
+                                                             int32_t *__restrict__ sym_col,
+                                                             int32_t *__restrict__ sym_w) {
+    const int64_t r = blockIdx.x, shift = lower_ptr[r + 1];
+    // a malformed row pointer has been flagged by the input check
+    const int64_t beg = max<int64_t>(row_ptr[r], 0), end = min(row_ptr[r + 1], n);
+    constexpr int kAhead = 8;
+    // positions in the output, from a multiple of 64 on
+    for (int64_t q0 = (beg + shift) / 64 * 64 + threadIdx.x; q0 < end + shift; q0 += 256 * kAhead) {
+        int32_t c[kAhead], x[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int64_t e = q0 + 256 * u - shift;
+            c[u] = e >= beg && e < end ? col[e] : 0;
+            x[u] = e >= beg && e < end && w ? w[e] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int64_t q = q0 + 256 * u, e = q - shift;
+            if (e < beg || e >= end || q >= 2 * n) continue;
+            __builtin_nontemporal_store(c[u], sym_col + q);
+            if (w) __builtin_nontemporal_store(x[u], sym_w + q);
+        }
+    }
+}
+
+// Edges per row from which that is faster than one thread per edge (2200 a
+// row: 1.99 -> 1.43 ms for 4.4e8).
+constexpr int64_t kLongRows = 256;
+
 // ---------------------------------------------------------------------------
 // Transpose of an upper triangle into the lower parts of its symmetric CSR
 // ---------------------------------------------------------------------------
@@ -324,9 +360,9 @@ __global__ void sym_upper_kernel(const int32_t *__restrict__ row, const int32_t 
 //     their places in the output.
 // A wavefront ranks kTrRounds rounds of its own contiguous items without a
 // barrier (its counts in LDS, in order), so a tile has eight barriers where the
-// sort above has three per round. The same edges now take 8.9 ms: 2.9 and 2.5
+// sort above has three per round. The same edges now take 8.3 ms: 2.9 and 2.5
 // in the passes (20 and 16 bytes an edge, 3.0 and 2.8 TB/s), 1.4 in the counts
-// and the check, 2.0 in the upper copy. Tiles of 6144 items (three workgroups
+// and the check, 1.4 in the upper copy. Tiles of 6144 items (three workgroups
 // a CU) took 4.2 and 3.5, of 16 384 (one) 2.7 and 2.6.
 constexpr int kTrThreads = 512;
 constexpr int kTrWaves = kTrThreads / 64;
@@ -774,7 +810,11 @@ hipError_t launch_transpose(const int64_t *row_ptr, const int32_t *row, const in
     else
         SLG_TRANSPOSE(1024);
 #undef SLG_TRANSPOSE
-    sym_upper_kernel<<<sort_grid(n, 256 * kFlat, 16384), 256, 0, st>>>(row, col, w, n, m, lower_ptr, sym_col, sym_w);
+    if (n / m >= kLongRows)
+        sym_upper_rows_kernel<<<(unsigned)m, 256, 0, st>>>(row_ptr, col, w, n, lower_ptr, sym_col, sym_w);
+    else
+        sym_upper_kernel<<<sort_grid(n, 256 * kFlat, 16384), 256, 0, st>>>(row, col, w, n, m, lower_ptr, sym_col,
+                                                                           sym_w);
     return hipGetLastError();
 }
 
