@@ -73,7 +73,7 @@ bool grant(slg_server *sv, Request *q, uint64_t bytes, bool *yield, bool optiona
     slg::ServeCore &c = *sv->core;
     std::unique_lock<std::mutex> lk(c.mu);
     if (optional && c.budget && c.used + bytes > c.budget) {
-        q->lean = true;
+        (sv->stop ? q->cancelled : q->lean) = true;
         return false;
     }
     if (c.budget && q->held + bytes > c.budget) return false;  // can never fit
