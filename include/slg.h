@@ -356,6 +356,14 @@ slg_status slg_context_set_dense(slg_context *ctx, int32_t min_ratio, int32_t mi
 slg_status slg_context_set_list_shortfall(slg_context *ctx, int64_t entries);
 
 /*
+ * For tests of launches that are split where a device takes no larger ones
+ * (no part of the method): plans created afterwards put at most `workgroups`
+ * into each launch of the hub tier. Results are identical. 0 (the default):
+ * as many as the device takes; workgroups < 0 is SLG_ERR_INVALID_ARG.
+ */
+slg_status slg_context_set_launch_limit(slg_context *ctx, int64_t workgroups);
+
+/*
  * Tuning of the plan shape, used by the autotuner: light_max = largest row
  * work (2-paths) sorted by one wavefront (<= 2048; 0 = default),
  * slot_work = 2-paths per heavy slot before a row is split (0 = default),

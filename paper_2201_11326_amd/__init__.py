@@ -124,6 +124,7 @@ def lib() -> ctypes.CDLL:
         "slg_context_set_tuning": (_i32, [_p, _i32, _i64, _i32]),
         "slg_context_set_dense": (_i32, [_p, _i32, _i32]),
         "slg_context_set_list_shortfall": (_i32, [_p, _i64]),
+        "slg_context_set_launch_limit": (_i32, [_p, _i64]),
         "slg_context_set_timing": (_i32, [_p, ctypes.c_int]),
         "slg_context_get_timing": (_i32, [_p, ctypes.POINTER(StageTime), _i32, ctypes.POINTER(_i32)]),
         "slg_context_reset_timing": (_i32, [_p]),
@@ -354,6 +355,11 @@ class Context:
         descriptor lists `entries` fewer places than counted, so their
         appends are refused and the plan fails with SLG_ERR_DEVICE."""
         self._check(lib().slg_context_set_list_shortfall(self.handle, int(entries)))
+
+    def set_launch_limit(self, workgroups: int):
+        """For tests: later plans put at most `workgroups` into each launch that
+        is split where the device takes no larger ones (0: as many as it takes)."""
+        self._check(lib().slg_context_set_launch_limit(self.handle, int(workgroups)))
 
     # -- measurement ---------------------------------------------------------
     def set_count_store(self, max_bytes: int, min_two_paths: int = 1 << 24):

@@ -72,6 +72,7 @@ struct slg_context {
     int64_t lstore_min = 0;                   // and fewest 2-paths for the light rows' store
     bool store_set = false;                   // the caller chose them
     int64_t list_shortfall = 0;  // error-path tests: heavy lists planned this much short
+    int64_t launch_limit = 0;    // tests: most workgroups per launch that may take several (0: HIP's)
     uint64_t budget = 0;
     bool has_alloc = false;
     slg_allocator alloc{};
@@ -366,6 +367,7 @@ struct slg_plan {
     bool hubs = false;             // dense rows may take the hub tier (decided on the device)
     int64_t hub_rows = 0;          // hub rows and slots of the block
     int64_t hub_slots = 0;
+    int64_t hub_window = 0;        // no hub row of the block has a slot before this window
     bool use_dstore = false;       // dense slots keep their survivors for the emit pass
     CountStore dstore{};
     int64_t dstore_cap = 0;        // entries of the dense store
@@ -384,6 +386,7 @@ struct slg_plan {
     int64_t store_limit = 0;
     int64_t store_min = 0, lstore_min = 0;
     int64_t list_shortfall = 0;
+    int64_t launch_limit = 0;
     int64_t plan_lo = 0, plan_hi = -1;  // rows the rows phase plans (-1: to the last)
     int64_t stored_ranks = 0;
     int64_t two_paths = 0;
@@ -722,7 +725,8 @@ struct AuxFork {
 
 // Hub rows [lo, hi) of the block's list.
 HubRows hub_range(const slg_plan *p, int64_t lo, int64_t hi) {
-    return {p->b.hub_rows, lo, hi, p->kept_rows, p->b.nslots, p->slot_base, p->b.hub, p->b.nib};
+    return {p->b.hub_rows, lo, hi, p->kept_rows, p->b.nslots, p->slot_base, p->b.hub, p->b.nib,
+            p->hub_window, p->launch_limit};
 }
 
 hipError_t enqueue_slots_count(slg_plan *p, hipStream_t st) {
@@ -984,13 +988,11 @@ slg_status plan_block(slg_plan *p, int64_t r0, int64_t r1) {
                                     reinterpret_cast<unsigned long long *>(b.counters + kCntHeavyWork),
                                     reinterpret_cast<unsigned long long *>(b.counters + kCntDenseWork), st));
         BUILD_HIP(launch_scans(ScanJobs().add(b.nslots, m, p->slot_base).add(b.bsize, m, b.bbase), b.part_m, st));
-        BUILD_HIP(launch_read_back(ReadBack()
-                                       .add(b.counters, 0, kCntTotal)
-                                       .add(p->slot_base + m, kHbSlots)
-                                       .add(b.work_pre + r0, kHbSlots + 1)
-                                       .add(b.bbase + m, kHbSlots + 2)
-                                       .add(b.work_pre + r1, kHbRange),
-                                   hb, st));
+        ReadBack rb;
+        rb.add(b.counters, 0, kCntTotal).add(p->slot_base + m, kHbSlots).add(b.work_pre + r0, kHbSlots + 1);
+        rb.add(b.bbase + m, kHbSlots + 2).add(b.work_pre + r1, kHbRange);
+        if (p->dense) rb.add(b.krow.pre + (r0 >> 6), kHbRange + 1);  // kept rows before r0's word
+        BUILD_HIP(launch_read_back(rb, hb, st));
         BUILD_HIP(hipStreamSynchronize(st));
         for (int c = 0; c < kNumLists; ++c) p->list_count[c] = hb[kCntClass + c];
         p->S = hb[kHbSlots];
@@ -1000,6 +1002,7 @@ slg_status plan_block(slg_plan *p, int64_t r0, int64_t r1) {
         p->dense_two_paths = hb[kCntDenseWork];
         p->hub_rows = hb[kCntHubRows];
         p->hub_slots = p->list_count[kNumLists - 1];
+        p->hub_window = p->dense ? (hb[kHbRange + 1] + 1) >> kDenseBits : 0;
     } else if (p->blocks && (p->row_lo != 0 || p->row_hi != m)) {
         return fail(ctx, SLG_ERR_INVALID_ARG, "internal error: all rows after a row block");
     }
@@ -1172,6 +1175,7 @@ slg_plan *plan_new(slg_context *ctx, slg_graph *g, const int32_t *s, int32_t num
     p->store_min = ctx->store_min;
     p->lstore_min = ctx->lstore_min;
     p->list_shortfall = ctx->list_shortfall;
+    p->launch_limit = ctx->launch_limit;
     return p;
 }
 
@@ -1736,6 +1740,13 @@ slg_status slg_context_set_list_shortfall(slg_context *ctx, int64_t entries) {
     if (!ctx) return SLG_ERR_INVALID_ARG;
     if (entries < 0) return fail(ctx, SLG_ERR_INVALID_ARG, "entries must be >= 0");
     ctx->list_shortfall = entries;
+    return SLG_OK;
+}
+
+slg_status slg_context_set_launch_limit(slg_context *ctx, int64_t workgroups) {
+    if (!ctx) return SLG_ERR_INVALID_ARG;
+    if (workgroups < 0) return fail(ctx, SLG_ERR_INVALID_ARG, "workgroups must be >= 0");
+    ctx->launch_limit = workgroups;
     return SLG_OK;
 }
 

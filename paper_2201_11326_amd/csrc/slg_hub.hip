@@ -21,11 +21,12 @@
 // each of its eight wavefronts covers 64 positions x 32 rows per step: four
 // position tiles x two row tiles. Positions are dealt to the tiles so that a
 // lane's 16 results of a row tile are 16 consecutive positions of one row.
-// Workgroups are numbered window-major, so those in flight read the same
-// window's 1 MiB of `nib` from L2.
+// Workgroups are numbered window-major (slg_grid.h), so those in flight read
+// the same window's 1 MiB of `nib` from L2.
 #include <limits.h>
 
 #include "slg_device.h"
+#include "slg_grid.h"
 #include "slg_internal.h"
 
 namespace slg {
@@ -447,14 +448,15 @@ __device__ __forceinline__ int wave_incl_scan_dpp(int x) {
 // KT: 1, 2 or SLG_MAX_S thresholds held in registers.
 template <int KT>
 __global__ __launch_bounds__(kHubThreads) __attribute__((amdgpu_waves_per_eu(4))) void hub_count_kernel(
-    Pruned g, HubRows h, EmitParams prm, int64_t groups, int64_t S, int64_t *__restrict__ slot_cnt) {
+    Pruned g, HubRows h, EmitParams prm, int64_t number0, int64_t groups, int64_t S, int64_t *__restrict__ slot_cnt) {
     constexpr int kStride = kCountRange + 16;
     __shared__ HubSmem<kHubRows> sm;
     __shared__ uint32_t cnt[kHubRows * kStride / 4];  // remainder overlaps of the range, 8 bits each
     __shared__ uint32_t tally[KT][kHubRows];
     const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
-    const int w = (int)(blockIdx.x / groups);
-    if (!hub_rows(sm, g, h, h.lo + (int64_t)(blockIdx.x % groups) * kHubRows, w)) return;
+    const int64_t number = number0 + blockIdx.x;
+    const int w = (int)(h.first_window + number / groups);
+    if (!hub_rows(sm, g, h, h.lo + number % groups * kHubRows, w)) return;
     for (int x = tid; x < kHubRows * kStride / 4; x += kHubThreads) cnt[x] = 0u;
     for (int x = tid; x < KT * kHubRows; x += kHubThreads) tally[x / kHubRows][x % kHubRows] = 0u;
     const int K = prm.k, s_min = prm.s[0];
@@ -642,7 +644,8 @@ __device__ __forceinline__ void hub_write_row(const EmitParams &prm, uint8_t *cr
 // 3.9 ms, after a counting pass that is 11 ms longer for writing them).
 template <int KT>
 __global__ __launch_bounds__(kHubThreads) __attribute__((amdgpu_waves_per_eu(4))) void hub_emit_kernel(
-    Pruned g, HubRows h, EmitParams prm, int64_t groups, int64_t S, const int64_t *__restrict__ slot_off) {
+    Pruned g, HubRows h, EmitParams prm, int64_t number0, int64_t groups, int64_t S,
+    const int64_t *__restrict__ slot_off) {
     constexpr int kStride = kEmitStep + 16;
     constexpr int kTile = kEmitRows * kStride / 4;
     constexpr int kProducers = kHubWaves / 2;
@@ -653,8 +656,9 @@ __global__ __launch_bounds__(kHubThreads) __attribute__((amdgpu_waves_per_eu(4))
     __shared__ long long base[KT][kEmitRows];          // the rows' next output positions
     __shared__ int ticket[2];                          // rows of a step taken, by parity
     const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
-    const int w = (int)(blockIdx.x / groups);
-    if (!hub_rows(sm, g, h, h.lo + (int64_t)(blockIdx.x % groups) * kEmitRows, w)) return;
+    const int64_t number = number0 + blockIdx.x;
+    const int w = (int)(h.first_window + number / groups);
+    if (!hub_rows(sm, g, h, h.lo + number % groups * kEmitRows, w)) return;
     for (int x = tid; x < 3 * kTile; x += kHubThreads) (&cnt[0][0])[x] = 0u;
     const int K = prm.k, s_min = prm.s[0];
     const int ja = w << kDenseBits;
@@ -805,20 +809,23 @@ hipError_t launch_hub(bool emit, const HubRows &h, const Pruned &g, const EmitPa
                       int64_t *slot_cnt, const int64_t *slot_off, hipStream_t st) {
     if (h.hi <= h.lo) return hipSuccess;
     if (!g.cid || !g.cid_row || !g.vs_cid || !g.vs_win || !h.nib || ep.row_s || ep.row_base || ep.s[0] > kHubMaxS) return hipErrorInvalidValue;
-    const int rows = emit ? kEmitRows : kHubRows;
-    const int64_t groups = (h.hi - h.lo + rows - 1) / rows, windows = (h.kept >> kDenseBits) + 1;
-    if (groups * windows > INT_MAX) return hipErrorInvalidValue;
-    const unsigned grid = (unsigned)(groups * windows);
-#define SLG_HUB(KT)                                                                                      \
-    do {                                                                                                \
-        if (emit)                                                                                       \
-            hub_emit_kernel<KT><<<grid, kHubThreads, 0, st>>>(g, h, ep, groups, slots, slot_off);        \
-        else                                                                                            \
-            hub_count_kernel<KT><<<grid, kHubThreads, 0, st>>>(g, h, ep, groups, slots, slot_cnt);       \
-    } while (0)
-    if (ep.k <= 1) SLG_HUB(1);
-    else if (ep.k <= 2) SLG_HUB(2);
-    else SLG_HUB(SLG_MAX_S);
+    const HubGrid grid(h.lo, h.hi, emit ? kEmitRows : kHubRows, h.kept, kDenseBits, h.first_window, kHubThreads,
+                       h.launch_limit);
+#define SLG_HUB(KT)                                                                                             \
+    for (int64_t base = 0; base < grid.total; base += grid.cap) {                                               \
+        const unsigned count = (unsigned)grid.count(base);                                                      \
+        if (emit)                                                                                               \
+            hub_emit_kernel<KT><<<count, kHubThreads, 0, st>>>(g, h, ep, base, grid.groups, slots, slot_off);   \
+        else                                                                                                    \
+            hub_count_kernel<KT><<<count, kHubThreads, 0, st>>>(g, h, ep, base, grid.groups, slots, slot_cnt);  \
+    }
+    if (ep.k <= 1) {
+        SLG_HUB(1)
+    } else if (ep.k <= 2) {
+        SLG_HUB(2)
+    } else {
+        SLG_HUB(SLG_MAX_S)
+    }
 #undef SLG_HUB
     return hipGetLastError();
 }

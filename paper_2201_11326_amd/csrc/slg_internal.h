@@ -105,9 +105,10 @@ struct HubInfo {
     int32_t vertex[kHubs];
 };
 
-// The hub rows [lo, hi) of a launch (ascending ids in `rows`) and what every
+// The hub rows [lo, hi) of a call (ascending ids in `rows`) and what every
 // launch reads: nib = kHubs fp4 values per rank of E_s (1.0: the hub lies in
-// the rank's row), zero up to the end of the last window.
+// the rank's row), zero up to the end of the last window. No row has a slot
+// before first_window. launch_limit: most workgroups per launch (0: HIP's).
 struct HubRows {
     const int32_t *rows;
     int64_t lo, hi, kept;
@@ -115,6 +116,7 @@ struct HubRows {
     const int64_t *slot_base;
     const HubInfo *info;
     const uint32_t *nib;
+    int64_t first_window, launch_limit;
 };
 
 // Slot table: a slot is (row i, hyperedge-id range) with its own output
