@@ -358,8 +358,9 @@ slg_status slg_context_set_list_shortfall(slg_context *ctx, int64_t entries);
 /*
  * For tests of launches that are split where a device takes no larger ones
  * (no part of the method): plans created afterwards put at most `workgroups`
- * into each launch of the hub tier. Results are identical. 0 (the default):
- * as many as the device takes; workgroups < 0 is SLG_ERR_INVALID_ARG.
+ * into each launch of the hub tier and of the light classes together. Results
+ * are identical. 0 (the default): as many as the device takes;
+ * workgroups < 0 is SLG_ERR_INVALID_ARG.
  */
 slg_status slg_context_set_launch_limit(slg_context *ctx, int64_t workgroups);
 

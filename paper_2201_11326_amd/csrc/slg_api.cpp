@@ -765,7 +765,7 @@ hipError_t enqueue_slots_count(slg_plan *p, hipStream_t st) {
             if ((e = launch_exclusive_scan_i32(p->lwork, m, p->lstore.off, b.part_light, lst)) != hipSuccess) return e;
         }
         if ((e = launch_light_count(p->lists, p->list_count, p->slots, p->pr, p->prm, p->slot_cnt,
-                                    p->use_lstore ? &p->lstore : nullptr, lst)) != hipSuccess)
+                                    p->use_lstore ? &p->lstore : nullptr, p->launch_limit, lst)) != hipSuccess)
             return e;
     }
     {
@@ -1238,7 +1238,8 @@ slg_status emit_range(slg_plan *p, int64_t r0, int64_t r1, int64_t s0, int64_t s
     {
         StageTimer tm(ctx, kStEmitLight, st);
         if (p->use_lstore)
-            SLG_HIP(ctx, launch_light_store_emit(p->lists, p->list_count, p->slots, p->lstore, prm, p->slot_off, st));
+            SLG_HIP(ctx, launch_light_store_emit(p->lists, p->list_count, p->slots, p->lstore, prm, p->slot_off,
+                                                 p->launch_limit, st));
         else
             for (int c = 0; c < kLightClasses; ++c)
                 SLG_HIP(ctx, launch_light(c, true, p->lists[c], p->list_count[c], p->slots, p->pr, prm, nullptr,

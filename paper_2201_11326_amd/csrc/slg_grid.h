@@ -28,4 +28,25 @@ struct HubGrid {
     int64_t count(int64_t base) const { return total - base < cap ? total - base : cap; }
 };
 
+// Rows of N classes, the last class first, `rows0` of class 0 and `rows` of
+// any other per workgroup, in launches of at most `cap` workgroups: next()
+// takes the next launch's rows and returns its workgroups (0: none are left).
+template <int N>
+struct ClassRuns {
+    int64_t begin[N] = {}, count[N] = {};  // this launch's rows of each class
+    unsigned first[N] = {};                // first workgroup of class N - 1, ..., 0
+    unsigned next(const int64_t *counts, int rows0, int rows, int64_t cap) {
+        int64_t grid = 0;
+        for (int r = 0; r < N; ++r) {
+            const int c = N - 1 - r;
+            const int64_t per = c ? rows : rows0, room = (cap - grid) * per;
+            begin[c] += count[c];
+            count[c] = counts[c] - begin[c] < room ? counts[c] - begin[c] : room;
+            first[r] = (unsigned)grid;
+            grid += (count[c] + per - 1) / per;
+        }
+        return (unsigned)grid;
+    }
+};
+
 }  // namespace slg

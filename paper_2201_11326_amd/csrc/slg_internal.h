@@ -281,13 +281,15 @@ hipError_t launch_bounds(const Pruned &g, const HeavyDesc *desc, int64_t count, 
 hipError_t launch_light(int cls, bool emit, const int32_t *list, int64_t count, const Slots &sl,
                         const Pruned &g, const EmitParams &ep, int64_t *slot_cnt,
                         const int64_t *slot_off, const LightStore *store, hipStream_t st);
-// The counting pass of all light classes.
+// The counting pass of all light classes (limit > 0: at most that many
+// workgroups per launch, here and below).
 hipError_t launch_light_count(const int32_t *const *lists, const int64_t *counts, const Slots &sl, const Pruned &g,
-                              const EmitParams &ep, int64_t *slot_cnt, const LightStore *store, hipStream_t st);
+                              const EmitParams &ep, int64_t *slot_cnt, const LightStore *store, int64_t limit,
+                              hipStream_t st);
 // Emit pass of all light classes from the light store.
 hipError_t launch_light_store_emit(const int32_t *const *lists, const int64_t *counts, const Slots &sl,
                                    const LightStore &store, const EmitParams &ep, const int64_t *slot_off,
-                                   hipStream_t st);
+                                   int64_t limit, hipStream_t st);
 // lw[i] = 2-paths of row i if it is in a light class, else 0.
 hipError_t launch_light_work(int64_t m, const uint8_t *rclass, const int64_t *work, int32_t *lw, hipStream_t st);
 // Persistent launch: `resident` workgroups (0 = a default) take slots from

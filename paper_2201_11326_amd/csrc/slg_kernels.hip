@@ -33,6 +33,7 @@
 #include <type_traits>
 
 #include "slg_device.h"
+#include "slg_grid.h"
 #include "slg_internal.h"
 
 namespace slg {
@@ -3225,18 +3226,23 @@ hipError_t launch_heavy_range(const HeavyDesc *desc, int64_t count, int64_t s0, 
 }
 
 namespace {
-// All light classes from one launch: `grid` workgroups, runs.first set.
-LightRuns light_runs(const int32_t *const *lists, const int64_t *counts, unsigned &grid) {
-    LightRuns runs{};
-    grid = 0;
-    for (int r = 0; r < kLightClasses; ++r) {
-        const int c = kLightClasses - 1 - r;
-        runs.list[c] = lists[c];
-        runs.count[c] = counts[c];
-        runs.first[r] = grid;
-        grid += counts[c] > 0 ? grid_for(counts[c], c ? 4 : 256) : 0;
+// launch(runs, workgroups) for all light classes together, in as many
+// launches as it takes (limit > 0: of at most that many workgroups).
+template <typename F>
+hipError_t light_launches(const int32_t *const *lists, const int64_t *counts, int64_t limit, F launch) {
+    ClassRuns<kLightClasses> part;
+    while (const unsigned grid = part.next(counts, 256, 4, max_workgroups(256, limit))) {
+        LightRuns runs;
+        for (int c = 0; c < kLightClasses; ++c) {
+            runs.list[c] = lists[c] + part.begin[c];
+            runs.count[c] = part.count[c];
+            runs.first[c] = part.first[c];
+        }
+        launch(runs, grid);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
-    return runs;
+    return hipSuccess;
 }
 
 // Rows of the sorting classes up to which they are counted in one launch. It
@@ -3246,7 +3252,8 @@ constexpr int64_t kLightTogether = 16384;
 }  // namespace
 
 hipError_t launch_light_count(const int32_t *const *lists, const int64_t *counts, const Slots &sl, const Pruned &g,
-                              const EmitParams &ep, int64_t *slot_cnt, const LightStore *store, hipStream_t st) {
+                              const EmitParams &ep, int64_t *slot_cnt, const LightStore *store, int64_t limit,
+                              hipStream_t st) {
     int64_t rows = 0;
     for (int c = 1; c < kLightClasses; ++c) rows += counts[c];
     if (rows > kLightTogether || rows == 0) {
@@ -3256,13 +3263,12 @@ hipError_t launch_light_count(const int32_t *const *lists, const int64_t *counts
         }
         return hipSuccess;
     }
-    unsigned grid;
-    const LightRuns runs = light_runs(lists, counts, grid);
-    if (store)
-        light_count_kernel<true><<<grid, 256, 0, st>>>(runs, sl, g, ep, slot_cnt, *store);
-    else
-        light_count_kernel<false><<<grid, 256, 0, st>>>(runs, sl, g, ep, slot_cnt, LightStore{});
-    return hipGetLastError();
+    return light_launches(lists, counts, limit, [&](const LightRuns &runs, unsigned grid) {
+        if (store)
+            light_count_kernel<true><<<grid, 256, 0, st>>>(runs, sl, g, ep, slot_cnt, *store);
+        else
+            light_count_kernel<false><<<grid, 256, 0, st>>>(runs, sl, g, ep, slot_cnt, LightStore{});
+    });
 }
 
 hipError_t launch_light(int cls, bool emit, const int32_t *list, int64_t count, const Slots &sl,
@@ -3311,12 +3317,10 @@ hipError_t launch_light(int cls, bool emit, const int32_t *list, int64_t count, 
 
 hipError_t launch_light_store_emit(const int32_t *const *lists, const int64_t *counts, const Slots &sl,
                                    const LightStore &store, const EmitParams &ep, const int64_t *slot_off,
-                                   hipStream_t st) {
-    unsigned grid;
-    const LightRuns runs = light_runs(lists, counts, grid);
-    if (!grid) return hipSuccess;
-    light_store_emit_kernel<<<grid, 256, 0, st>>>(runs, sl, store, ep, slot_off);
-    return hipGetLastError();
+                                   int64_t limit, hipStream_t st) {
+    return light_launches(lists, counts, limit, [&](const LightRuns &runs, unsigned grid) {
+        light_store_emit_kernel<<<grid, 256, 0, st>>>(runs, sl, store, ep, slot_off);
+    });
 }
 
 hipError_t launch_light_work(int64_t m, const uint8_t *rclass, const int64_t *work, int32_t *lw, hipStream_t st) {

@@ -56,3 +56,35 @@ def test_late_row_ranges():
         assert torch.equal(torch.cat([c[t] for c in got]), getattr(whole, f)), f
     g.release()
     ctx.close()
+
+
+@pytest.mark.parametrize("store", [True, False])
+@pytest.mark.parametrize("limit", [1, 2, 5, 33])
+def test_light_classes_in_many_launches(limit, store):
+    """Rows of every light class, against the oracle."""
+    import numpy as np
+    import hypergen as hg
+    import oracle
+    import paper_2201_11326_amd as slg
+    ptr, idx, at = [0], [], 0
+    for width, rows in ((3, 700), (5, 9), (12, 30), (17, 45), (24, 50), (33, 70), (46, 95)):
+        for r in range(rows):  # row r of a band shares width - d vertices with row r + d
+            idx.extend(range(at + r, at + r + width))
+            ptr.append(len(idx))
+        at += rows + width
+    inc = hg.from_csr(len(ptr) - 1, at, np.array(ptr, np.int64), np.array(idx, np.int32))
+    ctx = slg.Context(0)
+    if not store:
+        ctx.set_count_store(0)
+    ctx.set_launch_limit(limit)
+    g = ctx.register_incidence(inc)
+    p = ctx.plan(g, [1])
+    st = p.stats()
+    assert all(st[n] > 0 for n in slg.Plan.STAT_NAMES[1:8]), st
+    p.destroy()
+    for lg in ctx.line_graph(g, [1, 2, 9, 20]):
+        ref = oracle.line_graph(inc, lg.s)
+        for f, x in (("row_ptr", ref.row_ptr), ("row", ref.i), ("col", ref.j), ("w", ref.w)):
+            np.testing.assert_array_equal(getattr(lg, f).cpu().numpy(), x, err_msg=f"{lg.s} {f}")
+    g.release()
+    ctx.close()
