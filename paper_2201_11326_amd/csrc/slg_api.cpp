@@ -2194,6 +2194,8 @@ slg_status slg_symmetrize(slg_context *ctx, int64_t m, const int64_t *row_ptr, c
     if (!ctx || m < 0 || m >= (int64_t(1) << 31) || num_edges < 0 || !row_ptr || !sym_ptr ||
         (num_edges > 0 && (!row || !col || !sym_col)) || (!w) != (!sym_w))
         return fail(ctx, SLG_ERR_INVALID_ARG, "bad symmetrize arguments");
+    const char *const not_upper = "input is not an upper triangle sorted by (row, col)";
+    if (m == 0 && num_edges > 0) return fail(ctx, SLG_ERR_INVALID_ARG, "%s", not_upper);  // no vertex has an edge
     SLG_HIP(ctx, hipSetDevice(ctx->device));
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int64_t n = num_edges;
@@ -2228,7 +2230,7 @@ slg_status slg_symmetrize(slg_context *ctx, int64_t m, const int64_t *row_ptr, c
     SLG_HIP(ctx, hipStreamSynchronize(st));
     sc.release();
     if (ctx->pinned[0] & 1)
-        return fail(ctx, SLG_ERR_INVALID_ARG, "input is not an upper triangle sorted by (row, col)");
+        return fail(ctx, SLG_ERR_INVALID_ARG, "%s", not_upper);
     return SLG_OK;
 }
 

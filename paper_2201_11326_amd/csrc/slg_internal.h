@@ -429,7 +429,7 @@ hipError_t launch_symmetric(const int32_t *skey, const int32_t *srow, const int3
                             hipStream_t st);
 
 // The same from the upper triangle alone, checked on the way (err as
-// launch_check_upper), n > 0 and m that transpose_packs: two passes, the
+// launch_check_upper), n > 0 and m > 0 that transpose_packs: two passes, the
 // second straight into the output. hist, off: transpose_counts_size(n, m) and
 // one more; partials: scan_partials_size of it; buckets: 2050; key, w: n (w
 // null without weights).

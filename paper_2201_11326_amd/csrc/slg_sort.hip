@@ -781,7 +781,7 @@ int64_t transpose_counts_size(int64_t n, int64_t m) {
 hipError_t launch_transpose(const int64_t *row_ptr, const int32_t *row, const int32_t *col, const int32_t *w,
                             int64_t n, int64_t m, const TransposeScratch &t, int64_t *lower_ptr, int64_t *sym_ptr,
                             int32_t *sym_col, int32_t *sym_w, int *err, hipStream_t st) {
-    if (n <= 0 || !transpose_packs(m)) return hipErrorInvalidValue;
+    if (n <= 0 || m <= 0 || !transpose_packs(m)) return hipErrorInvalidValue;
     const int64_t chunk = transpose_chunk(n), chunks = (n + chunk - 1) / chunk;
     const int nb = transpose_bins(m);
     if (chunks + nb > INT_MAX) return hipErrorInvalidValue;
