@@ -312,15 +312,17 @@ __global__ void sym_upper_kernel(const int32_t *__restrict__ row, const int32_t 
 
 // The same by rows, one workgroup per row, where rows are long: the row's id
 // is not read, and every wavefront's writes but a row's first and last are
-// whole lines, past the caches.
+// whole lines, past the caches. Only for pointers that passed the check (err):
+// rows of others may overlap, up to n entries in each.
 __global__ __launch_bounds__(256) void sym_upper_rows_kernel(const int64_t *__restrict__ row_ptr,
                                                              const int32_t *__restrict__ col,
                                                              const int32_t *__restrict__ w, int64_t n,
                                                              const int64_t *__restrict__ lower_ptr,
                                                              int32_t *__restrict__ sym_col,
-                                                             int32_t *__restrict__ sym_w) {
+                                                             int32_t *__restrict__ sym_w,
+                                                             const int *__restrict__ err) {
+    if (*err) return;
     const int64_t r = blockIdx.x, shift = lower_ptr[r + 1];
-    // a malformed row pointer has been flagged by the input check
     const int64_t beg = max<int64_t>(row_ptr[r], 0), end = min(row_ptr[r + 1], n);
     constexpr int kAhead = 8;
     // positions in the output, from a multiple of 64 on
@@ -811,7 +813,7 @@ hipError_t launch_transpose(const int64_t *row_ptr, const int32_t *row, const in
         SLG_TRANSPOSE(1024);
 #undef SLG_TRANSPOSE
     if (n / m >= kLongRows)
-        sym_upper_rows_kernel<<<(unsigned)m, 256, 0, st>>>(row_ptr, col, w, n, lower_ptr, sym_col, sym_w);
+        sym_upper_rows_kernel<<<(unsigned)m, 256, 0, st>>>(row_ptr, col, w, n, lower_ptr, sym_col, sym_w, err);
     else
         sym_upper_kernel<<<sort_grid(n, 256 * kFlat, 16384), 256, 0, st>>>(row, col, w, n, m, lower_ptr, sym_col,
                                                                            sym_w);
