@@ -396,7 +396,7 @@ struct slg_plan {
     int64_t num_edges[SLG_MAX_S] = {};
     const slg::ReserveFn *reserve = nullptr;  // asked before each planning allocation phase
     uint64_t reserved = 0;                    // bytes granted by `reserve`
-    bool *optional = nullptr;                 // set where a store is kept that a lean plan leaves out
+    uint64_t *optional = nullptr;             // gets the bytes of the stores that a lean plan leaves out
 };
 
 struct slg_batch {
@@ -1051,9 +1051,9 @@ slg_status plan_block(slg_plan *p, int64_t r0, int64_t r1) {
         p->use_lstore = p->store_limit > 0 && lrows > 0 && p->two_paths >= p->lstore_min &&
                         (p->use_store ? bytes : 0) + lbytes <= p->store_limit;
         p->lwork = nullptr;
-        if (p->optional && ((p->use_store && p->heavy_two_paths < kStoreMinLean) ||
-                            (p->use_lstore && p->two_paths < kStoreMinLean)))
-            *p->optional = true;
+        if (p->optional)
+            *p->optional = (p->use_store && p->heavy_two_paths < kStoreMinLean ? bytes : 0) +
+                           (p->use_lstore && p->two_paths < kStoreMinLean ? lbytes : 0);
         if (p->use_lstore) {
             phase2.add(&p->lstore.key, lcap);
             phase2.add(&p->lstore.cnt, lcap);
@@ -2021,7 +2021,7 @@ void copy_tuning(slg_context *dst, const slg_context *src) {
 
 slg_status serve_query(slg_context *wctx, slg_graph *g, const int32_t *s, int32_t num_s, hipStream_t st,
                        const ReserveFn &reserve, const std::shared_ptr<ServeCore> &core, slg_result **out,
-                       uint64_t *scratch_bytes, uint64_t *output_bytes, bool lean, bool *optional) {
+                       uint64_t *scratch_bytes, uint64_t *output_bytes, bool lean, uint64_t *stores) {
     *out = nullptr;
     *scratch_bytes = 0;
     *output_bytes = 0;
@@ -2032,7 +2032,7 @@ slg_status serve_query(slg_context *wctx, slg_graph *g, const int32_t *s, int32_
     p->reserve = &reserve;
     if (!wctx->store_set) {
         if (lean) p->store_min = p->lstore_min = kStoreMinLean;
-        p->optional = lean ? nullptr : optional;
+        p->optional = lean ? nullptr : stores;
     }
     slg_status rc = plan_build(p);
     *scratch_bytes = p->reserved;

@@ -48,11 +48,11 @@ using ReserveFn = std::function<bool(uint64_t bytes)>;
 // with SLG_ERR_OUT_OF_MEMORY. Any error leaves nothing allocated; the
 // reservations granted so far are reported in *scratch_bytes /
 // *output_bytes for the caller to give back. lean: without the stores that
-// small plans keep by themselves; else *optional is set before the first
-// reservation that holds one.
+// small plans keep by themselves; else *stores is set to their bytes before
+// the reservation that holds them.
 slg_status serve_query(slg_context *wctx, slg_graph *g, const int32_t *s, int32_t num_s, hipStream_t st,
                        const ReserveFn &reserve, const std::shared_ptr<ServeCore> &core, slg_result **out,
-                       uint64_t *scratch_bytes, uint64_t *output_bytes, bool lean, bool *optional);
+                       uint64_t *scratch_bytes, uint64_t *output_bytes, bool lean, uint64_t *stores);
 
 // Device of a context / a registered graph's context.
 int context_device(const slg_context *ctx);

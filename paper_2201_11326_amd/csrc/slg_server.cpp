@@ -67,17 +67,25 @@ namespace {
 // Budget request of query q (runs on q's worker thread, inside a planning
 // phase). Returns false to refuse; *yield tells whether q should go back to
 // the queue (another query already waits) rather than fail.
-// optional: the query could do with less; rather than wait it is refused and
-// runs again without (q->lean).
-bool grant(slg_server *sv, Request *q, uint64_t bytes, bool *yield, bool optional) {
+// stores: bytes, among these or held already, of stores that the query could do
+// without. It is refused and runs again without them (q->lean) rather than
+// wait for the stores themselves (held == false), or for anything that would
+// fit without them, or for what can never fit beside them.
+bool grant(slg_server *sv, Request *q, uint64_t bytes, bool *yield, uint64_t stores, bool held) {
     slg::ServeCore &c = *sv->core;
     std::unique_lock<std::mutex> lk(c.mu);
-    if (optional && c.budget && c.used + bytes > c.budget) {
-        (sv->stop ? q->cancelled : q->lean) = true;
-        return false;
-    }
-    if (c.budget && q->held + bytes > c.budget) return false;  // can never fit
+    auto lean = [&] {
+        if (!stores || !c.budget || c.used + bytes <= c.budget) return false;
+        return !held || c.used + bytes - stores <= c.budget || q->held + bytes > c.budget;
+    };
+    if (!lean() && c.budget && q->held + bytes > c.budget) return false;  // can never fit
     while (c.budget && c.used + bytes > c.budget) {
+        if (!sv->stop && lean()) {
+            q->lean = true;
+            if (sv->waiter == q) sv->waiter = nullptr;
+            c.cv.notify_all();
+            return false;
+        }
         if (sv->stop) {
             q->cancelled = true;
             if (sv->waiter == q) sv->waiter = nullptr;
@@ -128,13 +136,18 @@ void worker_main(slg_server *sv, int wi) {
         ++sv->running;
         lk.unlock();
 
-        bool yield = false, optional = false;
+        bool yield = false, held = false;
+        uint64_t stores = 0;
         const bool lean = q->lean;
-        const slg::ReserveFn reserve = [&](uint64_t bytes) { return grant(sv, q, bytes, &yield, optional); };
+        const slg::ReserveFn reserve = [&](uint64_t bytes) {
+            if (!grant(sv, q, bytes, &yield, stores, held)) return false;
+            held = stores > 0;
+            return true;
+        };
         slg_result *r = nullptr;
         uint64_t scratch = 0, output = 0;
         const slg_status rc = slg::serve_query(w.ctx, q->g, q->s, q->k, w.st, reserve, sv->core, &r, &scratch,
-                                               &output, lean, &optional);
+                                               &output, lean, &stores);
         lk.lock();
         --sv->running;
         // the query's stream has drained: its scratch is free again
