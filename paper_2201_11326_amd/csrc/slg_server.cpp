@@ -163,10 +163,12 @@ void worker_main(slg_server *sv, int wi) {
         } else {
             c.used -= output;
             q->held -= output;
-            if ((yield || q->lean != lean) && !sv->stop) {
+            const bool again = yield || q->lean != lean;
+            if (again && !sv->stop) {
                 if (yield) ++sv->yields;
                 sv->queue.push_front(q);
             } else {
+                q->cancelled |= again;  // sent back as the server stopped
                 q->message = q->cancelled ? "server shut down" : slg_last_error(w.ctx);
                 finish(sv, q, q->cancelled ? SLG_ERR_CANCELLED : rc);
             }

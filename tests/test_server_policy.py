@@ -48,3 +48,10 @@ def test_a_query_runs_again_without_its_stores(program, scenario):
 
 def test_an_output_beyond_the_budget_is_refused(program):
     assert program("output_never_fits") == [f"status {slg.SLG_ERR_OUT_OF_MEMORY} attempts 2 message out of memory"]
+
+
+@pytest.mark.parametrize("scenario", ["shutdown_after_refusal", "shutdown_after_yield"])
+def test_a_query_sent_back_as_the_server_stops_is_cancelled(program, scenario):
+    """It would have run again: it has not failed."""
+    for line in program(scenario):
+        assert line.startswith(f"status {slg.SLG_ERR_CANCELLED} ") and line.endswith("message server shut down")
