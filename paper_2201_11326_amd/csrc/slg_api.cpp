@@ -105,8 +105,9 @@ constexpr int kCntFill = kCntErr + 1;           // kNumLists: append cursors of 
 constexpr int kCntHeavyWork = kCntFill + kNumLists;  // 2-paths in heavy rows
 constexpr int kCntPieces = kCntHeavyWork + 1;     // large-row pieces of row planning
 constexpr int kCntDenseWork = kCntPieces + 1;     // 2-paths in dense rows
-constexpr int kCntHubRows = kCntDenseWork + 1;    // hub rows (written with the dense 2-paths)
-constexpr int kCntTotal = kCntHubRows + 1;
+constexpr int kCntHubRows = kCntDenseWork + 1;    // hub rows and their 2-paths (written with the dense rows')
+constexpr int kCntHubWork = kCntHubRows + 1;
+constexpr int kCntTotal = kCntHubWork + 1;
 constexpr int kCntRoom = 32;
 static_assert(kCntTotal <= kCntRoom, "counter block");
 // With the hub tier its choice and histogram follow, cleared together.
@@ -365,8 +366,9 @@ struct slg_plan {
     int32_t dense_ratio = 0, dense_min = 0;
     int dense_grid = 0;
     bool hubs = false;             // dense rows may take the hub tier (decided on the device)
-    int64_t hub_rows = 0;          // hub rows and slots of the block
+    int64_t hub_rows = 0;          // hub rows, their slots and 2-paths in the block
     int64_t hub_slots = 0;
+    int64_t hub_two_paths = 0;
     int64_t hub_window = 0;        // no hub row of the block has a slot before this window
     bool use_dstore = false;       // dense slots keep their survivors for the emit pass
     CountStore dstore{};
@@ -961,6 +963,7 @@ slg_status plan_rows(slg_plan *p) {
     p->heavy_two_paths = hb[kCntHeavyWork];
     p->dense_two_paths = hb[kCntDenseWork];
     p->hub_rows = hb[kCntHubRows];
+    p->hub_two_paths = hb[kCntHubWork];
     p->hub_slots = p->list_count[kNumLists - 1];
     p->row_lo = 0;
     p->row_hi = m;
@@ -1001,6 +1004,7 @@ slg_status plan_block(slg_plan *p, int64_t r0, int64_t r1) {
         p->heavy_two_paths = hb[kCntHeavyWork];
         p->dense_two_paths = hb[kCntDenseWork];
         p->hub_rows = hb[kCntHubRows];
+        p->hub_two_paths = hb[kCntHubWork];
         p->hub_slots = p->list_count[kNumLists - 1];
         p->hub_window = p->dense ? (hb[kHbRange + 1] + 1) >> kDenseBits : 0;
     } else if (p->blocks && (p->row_lo != 0 || p->row_hi != m)) {
@@ -1041,11 +1045,11 @@ slg_status plan_block(slg_plan *p, int64_t r0, int64_t r1) {
         const int64_t bytes = p->heavy_two_paths * 4 + nh * 20 + 16;
         p->use_store = nh > 0 && p->store_limit > 0 && bytes <= p->store_limit &&
                        p->heavy_two_paths >= p->store_min;
-        // the light rows' pairs: at most their 2-paths (all but the heavy and dense ones)
+        // the light rows' pairs: at most their 2-paths (all but the heavy, dense and hub ones)
         // a small plan of all rows lays them out by the 2-paths of every row,
         // whose prefix it has
         const bool whole = r0 == 0 && r1 == m && p->two_paths < kWholeStore;
-        const int64_t lrows = p->two_paths - p->heavy_two_paths - p->dense_two_paths;
+        const int64_t lrows = p->two_paths - p->heavy_two_paths - p->dense_two_paths - p->hub_two_paths;
         const int64_t lcap = whole ? p->two_paths : lrows;
         const int64_t lbytes = lcap * 6 + m * (whole ? 4 : 16) + 16;
         p->use_lstore = p->store_limit > 0 && lrows > 0 && p->two_paths >= p->lstore_min &&
@@ -1135,7 +1139,7 @@ slg_status plan_block(slg_plan *p, int64_t r0, int64_t r1) {
     wk[kWkBlocks] += 1;
     wk[kWkTwoPaths] += p->two_paths;
     wk[kWkHeavyTwoPaths] += p->heavy_two_paths;
-    wk[kWkDenseTwoPaths] += p->dense_two_paths;
+    wk[kWkDenseTwoPaths] += p->dense_two_paths + p->hub_two_paths;
     for (int k = 0; k < K; ++k) wk[kWkEdges] += p->num_edges[k];
     wk[kWkHeavyEdges] += p->heavy_edges;
     wk[kWkDenseEdges] += p->dense_edges;
@@ -1648,7 +1652,7 @@ slg_status slg_plan_stats(const slg_plan *p, int64_t *out, int32_t cap, int32_t 
     vals[13] = p->heavy_edges;
     vals[14] = p->stored_ranks;
     vals[15] = p->list_count[kLightClasses + 2] + p->hub_slots;
-    vals[16] = p->dense_two_paths;
+    vals[16] = p->dense_two_paths + p->hub_two_paths;
     vals[17] = p->dense_edges;
     vals[18] = p->dense_kept;
     vals[19] = p->dense_stored > p->dense_kept ? 1 : 0;

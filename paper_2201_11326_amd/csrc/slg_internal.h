@@ -241,7 +241,7 @@ hipError_t launch_vs_cid(int64_t n, int64_t m, int64_t nnz, const int64_t *vs_pt
 // K1/K2: per kept row, tail offsets, 2-path work, last partner, slot count.
 // dense_ratio = 0 keeps every row off the dense tier (then g.cid may be
 // null); with hub->use (hub may be null) dense rows are hub rows. dense_work
-// gets the 2-paths of dense and hub rows, dense_work[1] the hub rows.
+// gets the 2-paths of dense rows, the number of hub rows and their 2-paths.
 // Rows outside [row_lo, row_hi) are planned as pruned rows (no work, no
 // slots); their member tails are not located.
 hipError_t launch_row_plan(const Pruned &g, int32_t s_min, int32_t light_max, int64_t slot_work, int64_t row_lo,

@@ -337,7 +337,7 @@ struct RowPlanOut {
     int32_t dense_ratio;  // the dense tier's rule (0: off)
     int32_t dense_min;
     const HubInfo *hub;  // the hub tier's choice, or null
-    unsigned long long *dense_work;  // 2-paths of dense and hub rows, then the number of hub rows
+    unsigned long long *dense_work;  // 2-paths of dense rows, then the number of hub rows and their 2-paths
 };
 
 // Members p[u] of rows i[u] (in[u]: this lane has one): their tails, the tail
@@ -397,8 +397,7 @@ __device__ __forceinline__ void plan_members(const Pruned &g, const int (&i)[kPl
 }
 
 // Tier, slot count and boundary-table size of row i from its totals. hwork
-// (LDS): the workgroup's 2-paths of heavy rows, of dense and hub rows, and
-// its hub rows. A
+// (LDS): the workgroup's 2-paths of heavy rows, then what dense_work gets. A
 // heavy row goes to the dense tier when its candidate partners (the kept
 // rows in (i, jm]) number at least dense_min and it has at least
 // dense_ratio 2-paths per eight candidates: its slots are then the aligned
@@ -439,8 +438,11 @@ __device__ __forceinline__ void plan_finish(const Pruned &g, int64_t i, int64_t 
     o.bsize[i] = cls >= kHeavy && cls != kDenseHub ? (ns + 1) * (p1 - p0) : 0;  // hub rows keep no boundaries
     if (cls != kNone) atomicAdd(&ccount[cls - 1], (unsigned long long)ns);
     if (cls == kHeavy || cls == kHeavyWide) atomicAdd(hwork, (unsigned long long)w);
-    if (cls == kDense || cls == kDenseHub) atomicAdd(hwork + 1, (unsigned long long)w);
-    if (cls == kDenseHub) atomicAdd(hwork + 2, 1ull);
+    if (cls == kDense) atomicAdd(hwork + 1, (unsigned long long)w);
+    if (cls == kDenseHub) {
+        atomicAdd(hwork + 2, 1ull);
+        atomicAdd(hwork + 3, (unsigned long long)w);
+    }
 }
 
 // Small rows, ROWS of them per wavefront, and the piece list of the large
@@ -457,11 +459,11 @@ __global__ __launch_bounds__(256) void row_plan_kernel(Pruned g, int32_t s_min, 
                                                        int64_t *__restrict__ pieces, int64_t pieces_cap,
                                                        unsigned long long *__restrict__ num_pieces) {
     __shared__ unsigned long long ccount[kNumLists];
-    __shared__ unsigned long long hwork[3];
+    __shared__ unsigned long long hwork[4];
     __shared__ int pre[4][64], pos[4][64], rjm[4][64], rbad[4][64];
     __shared__ unsigned long long rw[4][64];
     if (threadIdx.x < kNumLists) ccount[threadIdx.x] = 0;
-    if (threadIdx.x < 3) hwork[threadIdx.x] = 0;
+    if (threadIdx.x < 4) hwork[threadIdx.x] = 0;
     __syncthreads();
     const int lane = lane_id(), wv = threadIdx.x >> 6;
     const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x / 64);
@@ -546,7 +548,7 @@ __global__ __launch_bounds__(256) void row_plan_kernel(Pruned g, int32_t s_min, 
     if (threadIdx.x < kNumLists && ccount[threadIdx.x])
         atomicAdd(&class_count[threadIdx.x], ccount[threadIdx.x]);
     if (threadIdx.x == 0 && hwork[0]) atomicAdd(heavy_work, hwork[0]);
-    if (threadIdx.x < 2 && hwork[1 + threadIdx.x]) atomicAdd(o.dense_work + threadIdx.x, hwork[1 + threadIdx.x]);
+    if (threadIdx.x < 3 && hwork[1 + threadIdx.x]) atomicAdd(o.dense_work + threadIdx.x, hwork[1 + threadIdx.x]);
 }
 
 // One wavefront per piece of a large row: the piece's tails and its largest
@@ -608,9 +610,9 @@ __global__ __launch_bounds__(256) void row_piece_finish_kernel(Pruned g, int32_t
                                                                const int64_t *__restrict__ piece_w,
                                                                const int32_t *__restrict__ piece_jm) {
     __shared__ unsigned long long ccount[kNumLists];
-    __shared__ unsigned long long hwork[3];
+    __shared__ unsigned long long hwork[4];
     if (threadIdx.x < kNumLists) ccount[threadIdx.x] = 0;
-    if (threadIdx.x < 3) hwork[threadIdx.x] = 0;
+    if (threadIdx.x < 4) hwork[threadIdx.x] = 0;
     __syncthreads();
     const int64_t count = min((int64_t)*num_pieces, pieces_cap);
     for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < count;
@@ -633,7 +635,7 @@ __global__ __launch_bounds__(256) void row_piece_finish_kernel(Pruned g, int32_t
     if (threadIdx.x < kNumLists && ccount[threadIdx.x])
         atomicAdd(&class_count[threadIdx.x], ccount[threadIdx.x]);
     if (threadIdx.x == 0 && hwork[0]) atomicAdd(heavy_work, hwork[0]);
-    if (threadIdx.x < 2 && hwork[1 + threadIdx.x]) atomicAdd(o.dense_work + threadIdx.x, hwork[1 + threadIdx.x]);
+    if (threadIdx.x < 3 && hwork[1 + threadIdx.x]) atomicAdd(o.dense_work + threadIdx.x, hwork[1 + threadIdx.x]);
 }
 
 // A row block: rows outside [r0, r1) get no slots, no class and no boundary
@@ -650,9 +652,10 @@ __global__ __launch_bounds__(256) void block_mask_kernel(int64_t m, int64_t r0, 
                                                          unsigned long long *__restrict__ heavy_work,
                                                          unsigned long long *__restrict__ dense_work) {
     __shared__ unsigned long long cc[kNumLists];
-    __shared__ unsigned long long hw, dw, hr;
+    __shared__ unsigned long long hw, dw[3];
     if (threadIdx.x < kNumLists) cc[threadIdx.x] = 0;
-    if (threadIdx.x == 0) hw = dw = hr = 0;
+    if (threadIdx.x == 0) hw = 0;
+    if (threadIdx.x < 3) dw[threadIdx.x] = 0;
     __syncthreads();
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) {
@@ -664,14 +667,16 @@ __global__ __launch_bounds__(256) void block_mask_kernel(int64_t m, int64_t r0, 
         bsize[i] = in ? bsize_all[i] : 0;
         if (c != kNone) atomicAdd(&cc[c - 1], (unsigned long long)ns);
         if (c == kHeavy || c == kHeavyWide) atomicAdd(&hw, (unsigned long long)work[i]);
-        if (c == kDense || c == kDenseHub) atomicAdd(&dw, (unsigned long long)work[i]);
-        if (c == kDenseHub) atomicAdd(&hr, 1ull);
+        if (c == kDense) atomicAdd(&dw[0], (unsigned long long)work[i]);
+        if (c == kDenseHub) {
+            atomicAdd(&dw[1], 1ull);
+            atomicAdd(&dw[2], (unsigned long long)work[i]);
+        }
     }
     __syncthreads();
     if (threadIdx.x < kNumLists && cc[threadIdx.x]) atomicAdd(&class_count[threadIdx.x], cc[threadIdx.x]);
     if (threadIdx.x == 0 && hw) atomicAdd(heavy_work, hw);
-    if (threadIdx.x == 0 && dw) atomicAdd(dense_work, dw);
-    if (threadIdx.x == 0 && hr) atomicAdd(dense_work + 1, hr);
+    if (threadIdx.x < 3 && dw[threadIdx.x]) atomicAdd(dense_work + threadIdx.x, dw[threadIdx.x]);
 }
 
 // Tier lists filled by fill_slots_kernel.
