@@ -222,8 +222,8 @@ slg_status slg_context_reset_timing(slg_context *ctx);
  * dense slots; [4] edges, summed over the thresholds; [5] edges of heavy
  * slots; [6] edges of dense slots; [7] dense slots; [8] survivors the
  * dense store kept; [9] blocks whose dense store was full (some slots
- * walked their 2-paths again). *count (may be NULL) gets the number
- * written.
+ * walked their 2-paths again); [10] 2-paths of those dense slots that the
+ * hub tier counts. *count (may be NULL) gets the number written.
  */
 slg_status slg_context_get_work(const slg_context *ctx, int64_t *out, int32_t cap, int32_t *count);
 

@@ -384,7 +384,7 @@ class Context:
         self._check(lib().slg_context_reset_timing(self.handle))
 
     WORK_NAMES = ("blocks", "two_paths", "heavy_two_paths", "dense_two_paths", "edges", "heavy_edges",
-                  "dense_edges", "dense_slots", "dense_stored", "dense_store_full_blocks")
+                  "dense_edges", "dense_slots", "dense_stored", "dense_store_full_blocks", "hub_two_paths")
 
     def work(self) -> dict:
         """Work of the counting passes since the last reset_timing()."""

@@ -37,7 +37,7 @@ struct PendingTime {
 // and row blocks) since the last reset.
 enum Work {
     kWkBlocks, kWkTwoPaths, kWkHeavyTwoPaths, kWkDenseTwoPaths, kWkEdges, kWkHeavyEdges, kWkDenseEdges,
-    kWkDenseSlots, kWkDenseStored, kWkDenseRewalk, kNumWork
+    kWkDenseSlots, kWkDenseStored, kWkDenseRewalk, kWkHubTwoPaths, kNumWork
 };
 
 // Heavy 2-paths from which a plan keeps the heavy slots' store by itself: two
@@ -905,7 +905,8 @@ slg_status plan_rows(slg_plan *p) {
         phase1.add(&b.vs_cid, nnz + kDensePad);
         phase1.add(&b.vs_win, nnz + kDensePad);  // the dense walk may load (not count) past the end
     }
-    // smaller graphs never have the 2-paths the hub tier asks for
+    // (of fewer incidences than 2^17 the hub rows have at most some 4e9 2-paths:
+    // they keep the dense tier's walk, without a look at the degrees)
     p->hubs = p->dense && nnz >= (1 << 17) && m >= kDenseWindow && p->s_min <= kHubMaxS;
     if (p->blocks) {
         phase1.add(&b.nslots_all, m);
@@ -1145,6 +1146,7 @@ slg_status plan_block(slg_plan *p, int64_t r0, int64_t r1) {
     wk[kWkDenseEdges] += p->dense_edges;
     wk[kWkDenseSlots] += p->list_count[kLightClasses + 2] + p->hub_slots;
     wk[kWkDenseStored] += p->dense_kept;
+    wk[kWkHubTwoPaths] += p->hub_two_paths;
     wk[kWkDenseRewalk] += (p->list_count[kLightClasses + 2] > 0 && p->dense_stored > p->dense_kept) ? 1 : 0;
     return SLG_OK;
 }
@@ -2139,7 +2141,7 @@ slg_status slg_components_noalloc(slg_context *ctx, slg_graph *g, int32_t s, con
     // two counters are cleared here and every parent is written by cc_init
     int64_t *dev = static_cast<int64_t *>(ctx->noalloc);  // [0] roots, [1] error flags
     int32_t *parent = reinterpret_cast<int32_t *>(dev + 2);
-    // the hook's bits are used up to 2^21 hyperedges: they fit behind the parents
+    // the hook's bits are used up to 1,245,184 hyperedges: they fit behind the parents
     uint32_t *bits = reinterpret_cast<uint32_t *>(parent + m);
     if (m + edge_bits_words(m, num_edges) > kNoAllocRows)
         return fail(ctx, SLG_ERR_INVALID_ARG, "internal error: the fixed scratch is too small");

@@ -31,7 +31,7 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-KERNEL_SRC = os.path.join(HERE, "csrc", "slg_kernels.hip")
+KERNEL_SRCS = [os.path.join(HERE, "csrc", name) for name in ("slg_kernels.hip", "slg_hub.hip")]
 COPY_BYTES = 1 << 30
 
 
@@ -132,10 +132,10 @@ def counter_per_kernel(db: str, counter: str):
 
 HEAVY_KERNELS = ("heavy_kernel<false, false, true>", "heavy_kernel<false, false, false>",
                  "heavy_store_emit_kernel<4, false>", "heavy_kernel<true, false, false>")
-DENSE_KERNELS = ("dense_kernel<false>", "heavy_store_emit_kernel<4, true>", "dense_kernel<true>")
+DENSE_KERNELS = ("hub_count_kernel<2>", "hub_emit_kernel<2>", "dense_kernel<false>", "heavy_store_emit_kernel<4, true>", "dense_kernel<true>")
 WORKLOADS = {  # probe -> (title, kernels)
     "power_law": ("the heavy-tier kernels (power-law ensemble S={1,2,4,8})", HEAVY_KERNELS),
-    "large_skewed": ("the dense-tier kernels (large skewed workload at full size, one row range, S={8,16})",
+    "large_skewed": ("the hub-tier and dense-tier kernels (large skewed workload at full size, one row range, S={8,16})",
                      DENSE_KERNELS),
 }
 
@@ -151,8 +151,11 @@ def traffic(fetch_db: str, write_db: str, workload: str = "power_law") -> str:
     ck = max(copy, key=lambda k: max(f[k])) if copy else None
     fetch_factor = COPY_BYTES / (max(f[ck]) * 1024) if ck else 1.0
     write_factor = COPY_BYTES / (max(w.get(ck, [0])) * 1024) if ck and w.get(ck) else 1.0
-    with open(KERNEL_SRC, "rb") as fh:
-        sha = hashlib.sha256(fh.read()).hexdigest()
+    h = hashlib.sha256()
+    for path in KERNEL_SRCS:
+        with open(path, "rb") as fh:
+            h.update(fh.read())
+    sha = h.hexdigest()
     title, kernels = WORKLOADS[workload]
     lines = [
         f"# HBM traffic of {title}",
