@@ -37,14 +37,17 @@ if ROOT not in sys.path:
 
 S_SET = [1, 2, 4, 8]
 PEAK_HBM_GBS = 8000.0  # MI355X HBM3E
-KERNEL_SRC = os.path.join(ROOT, "paper_2201_11326_amd", "csrc", "slg_kernels.hip")
+KERNEL_SRCS = [os.path.join(ROOT, "paper_2201_11326_amd", "csrc", name) for name in ("slg_kernels.hip", "slg_hub.hip")]
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "heavy_tier_power_law_traffic.md")
 METRIC = "2-paths traversed/sec + s-line edges/sec at 1 GPU; p50/p99 query latency"
 
 
 def kernel_source_hash() -> str:
-    with open(KERNEL_SRC, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+    h = hashlib.sha256()
+    for path in KERNEL_SRCS:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 DENSE_TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "dense_tier_large_skewed_traffic.md")
@@ -58,8 +61,9 @@ LARGE_STORE_GIB = 160.0
 def measured_traffic(kernel: str, profile: str = TRAFFIC_PROFILE, work_per_launch: float = None):
     """HBM bytes per launch of `kernel` from the committed PMC summary, if it
     was taken on the current kernel source; else None. Where the summary
-    states the 2-paths of its launches (a probe whose launches are smaller
-    than the bench's), the bytes are scaled to `work_per_launch` 2-paths."""
+    states the work of its launches (2-paths of a counting pass, edges of an
+    emit pass: a probe whose launches are smaller than the bench's), the bytes
+    are scaled to `work_per_launch` of it."""
     try:
         text = open(profile).read()
     except OSError:
@@ -71,7 +75,7 @@ def measured_traffic(kernel: str, profile: str = TRAFFIC_PROFILE, work_per_launc
         name = block.split("\n", 1)[0].strip()
         m_bytes = re.search(r"hbm_bytes_per_launch:\s*([0-9.eE+]+)", block)
         if name == kernel and m_bytes:
-            m_work = re.search(r"dense_two_paths_per_launch:\s*([0-9.eE+]+)", block)
+            m_work = re.search(r"dense_(?:two_paths|edges)_per_launch:\s*([0-9.eE+]+)", block)
             if m_work and work_per_launch:
                 return float(m_bytes.group(1)) * work_per_launch / float(m_work.group(1))
             return float(m_bytes.group(1))
@@ -826,31 +830,35 @@ def bench_large_skewed(args) -> int:
     assert work["two_paths"] == timed_two_paths, (work, timed_two_paths)
     assert sum(edges) == work["edges"], (edges, work)
     ms_per_step = 1e3 * elapsed / args.steps
-    # the dominant kernel: the dense tier's counting pass, 4 B read per
-    # 2-path of its slots (algorithmic bytes, the scope table's unit)
+    # the dominant kernel: the dense and hub slots' emit pass, 12 B written per
+    # edge. Their counting pass takes the 2-paths through the heaviest vertices
+    # as matrix products and never reads them one by one: only the others have
+    # the scope table's 4 B
     launches, count_ms = stages.get("count_dense", (0, 0.0))
-    dense_bytes = 4 * work["dense_two_paths"]
-    achieved = dense_bytes / (count_ms / 1e3) / 1e9 if count_ms > 0 else None
     emit_launches, emit_ms = stages.get("emit_dense", (0, 0.0))
+    emit_bytes = 12 * work["dense_edges"]
+    achieved = emit_bytes / (emit_ms / 1e3) / 1e9 if emit_ms > 0 else None
     roofline = {"bound": "hbm", "achieved": achieved, "peak": PEAK_HBM_GBS, "unit": "GB/s",
-                "frac": achieved / PEAK_HBM_GBS if achieved else None, "traffic": measured_traffic("dense_kernel<false>", DENSE_TRAFFIC_PROFILE,
-                                                                                     work["dense_two_paths"] / max(launches, 1)),
-                "kernel": "hub_count_kernel and dense_kernel<false> (count_dense)", "launches": launches,
-                "avg_launch_ms": count_ms / max(launches, 1),
-                "algorithmic_bytes_per_launch": dense_bytes / max(launches, 1),
-                "overhead_bytes_per_launch": {"dense_store_written": 4 * work["dense_stored"] / max(launches, 1)},
-                "sq_counters": measured_sq("dense_kernel<false>", DENSE_SQ_PROFILE),
-                "note": "2-paths through the heaviest vertices are counted with matrix instructions and never read "
-                        "one by one, so the algorithmic bytes exceed what HBM delivers; `traffic` is the measured "
-                        "HBM bytes per launch",
-                "emit": {"kernel": "hub_emit_kernel and heavy_store_emit_kernel<4, true> (emit_dense)",
-                         "launches": emit_launches, "ms": emit_ms,
-                         "algorithmic_bytes": 12 * work["dense_edges"],
-                         "achieved_gbs": 12 * work["dense_edges"] / (emit_ms / 1e3) / 1e9 if emit_ms > 0 else None}}
+                "frac": achieved / PEAK_HBM_GBS if achieved else None,
+                "traffic": measured_traffic("hub_emit_kernel<2>", DENSE_TRAFFIC_PROFILE,
+                                            work["dense_edges"] / max(emit_launches, 1)),
+                "kernel": "hub_emit_kernel<2> and heavy_store_emit_kernel<4, true> (emit_dense)",
+                "launches": emit_launches, "avg_launch_ms": emit_ms / max(emit_launches, 1),
+                "algorithmic_bytes_per_launch": emit_bytes / max(emit_launches, 1),
+                "sq_counters": measured_sq("hub_emit_kernel<2>", DENSE_SQ_PROFILE),
+                "count": {"kernel": "hub_count_kernel<2> and dense_kernel<false> (count_dense)",
+                          "launches": launches, "ms": count_ms,
+                          "two_paths_in_products": work["hub_two_paths"],
+                          "two_paths_walked": work["dense_two_paths"] - work["hub_two_paths"],
+                          "dense_store_written_bytes": 4 * work["dense_stored"],
+                          "traffic": measured_traffic("hub_count_kernel<2>", DENSE_TRAFFIC_PROFILE,
+                                                      work["hub_two_paths"] / max(launches, 1)),
+                          "sq_counters": measured_sq("hub_count_kernel<2>", DENSE_SQ_PROFILE)}}
     edges_total = sum(edges)
     nrows_timed = cuts[B] - cuts[args.warmup]
     step_bytes = (4 * timed_two_paths + 12 * edges_total
                   + args.steps * (8 * inc.nnz + 8 * (inc.m + inc.n)) + 8 * (nrows_timed + args.steps) * len(S))
+    moved_bytes = step_bytes - 4 * work["hub_two_paths"]  # without the 2-paths that are not read
     cpu = None if args.no_cpu_baseline else cpu_baseline(inc, args.cpu_seconds, S, size_min=S[0])
     line = {
         "metric": METRIC, "value": timed_two_paths / elapsed, "unit": "2-paths/s", "n_gpus": 1,
@@ -867,6 +875,7 @@ def bench_large_skewed(args) -> int:
         "edges_timed": edges, "edges_per_s": edges_total / elapsed,
         "p50_ms": 1e3 * percentile(lat, 0.5), "p99_ms": 1e3 * percentile(lat, 0.99),
         "step_roofline_frac": (step_bytes / elapsed) / (PEAK_HBM_GBS * 1e9),
+        "step_roofline_frac_without_products": (moved_bytes / elapsed) / (PEAK_HBM_GBS * 1e9),
         "stage_ms_per_step": {k: v[1] / args.steps for k, v in stages.items()},
         "work_timed": work, "chunks_timed": chunks[0],
         "roofline": roofline, "cpu_baseline": cpu, "generate_s": t_gen,
