@@ -2,6 +2,7 @@
 #pragma once
 
 #include "slg_internal.h"
+#include "slg_position.h"
 
 namespace slg {
 namespace {
@@ -119,7 +120,7 @@ __device__ __forceinline__ void stage_params(EmitParams *dst, const EmitParams &
 __device__ __forceinline__ int lower_bound_i32(const int32_t *__restrict__ a, int lo, int hi,
                                                int key) {
     while (lo < hi) {
-        int mid = (lo + hi) >> 1;
+        const int mid = middle(lo, hi);
         if (a[mid] < key)
             lo = mid + 1;
         else

@@ -369,7 +369,7 @@ __device__ __forceinline__ void plan_members(const Pruned &g, const int (&i)[kPl
         more = false;
 #pragma unroll
         for (int u = 0; u < kPlanAhead; ++u) {
-            mid[u] = (a[u] + e[u]) >> 1;
+            mid[u] = middle(a[u], e[u]);
             x[u] = a[u] < e[u] ? g.vs_idx[mid[u]] : 0;
         }
 #pragma unroll
@@ -2122,7 +2122,7 @@ __device__ __forceinline__ void bound_members(const HeavyDesc &d, int64_t p0, co
             more = false;
 #pragma unroll
             for (int u = 0; u < AHEAD; ++u) {
-                mid[u] = (lo[u] + hi[u]) >> 1;
+                mid[u] = middle(lo[u], hi[u]);
                 x[u] = lo[u] < hi[u] ? vs_idx[mid[u]] : 0;
             }
 #pragma unroll
