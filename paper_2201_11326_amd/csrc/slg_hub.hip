@@ -352,8 +352,8 @@ __device__ __forceinline__ void hub_cursors(HubSmem<ROWS> &sm, const Pruned &g, 
 // Adds up to eight places (those of list positions [a, last) in [from, to);
 // lists ascend and start at `from` or later) of the aligned block at blk to
 // the row's counters; returns how many.
-__device__ __forceinline__ int hub_add_block(uint32_t *cnt, int row, uint4 v, int blk, int a, int last, int from,
-                                             int to) {
+__device__ __forceinline__ int hub_add_block(uint32_t *cnt, int row, uint4 v, unsigned blk, unsigned a, unsigned last,
+                                             int from, int to) {
     const uint32_t x[4] = {v.x, v.y, v.z, v.w};
     int n = 0;
 #pragma unroll
@@ -383,33 +383,34 @@ __device__ __forceinline__ void hub_count_rest(HubSmem<ROWS> &sm, const Pruned &
         constexpr int kAhead = 4;
         const int sub = tid & 3, groups = threads / 4;
         for (int m0 = tid >> 2; m0 - (tid >> 2) < members; m0 += groups * kAhead) {
-            int a[kAhead], end[kAhead], row[kAhead];
+            unsigned a[kAhead], end[kAhead];  // blocks after the last may start past 2^31
+            int row[kAhead];
             uint4 v[kAhead];
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) {
                 const int x = m0 + u * groups;
                 const bool in = x < members;
-                a[u] = in ? sm.cur[x] : 0;
-                end[u] = in ? sm.end[x] : 0;
+                a[u] = in ? (unsigned)sm.cur[x] : 0u;
+                end[u] = in ? (unsigned)sm.end[x] : 0u;
                 row[u] = in ? sm.mrow[x] * stride : 0;
-                const int blk = (a[u] & ~7) + 8 * sub;
+                const unsigned blk = block_at(a[u], sub);
                 v[u] = blk < end[u] ? *reinterpret_cast<const uint4 *>(g.vs_win + blk) : make_uint4(0u, 0u, 0u, 0u);
             }
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) {
                 bool more = a[u] < end[u];
                 while (__any(more)) {
-                    const int b0 = a[u] & ~7, blk = b0 + 8 * sub;
-                    int n = more ? hub_add_block(cnt, row[u], v[u], blk, a[u], min(end[u], blk + 8), from, to) : 0;
+                    const unsigned b0 = block_at(a[u]), blk = block_at(a[u], sub);
+                    int n = more ? hub_add_block(cnt, row[u], v[u], blk, a[u], min(end[u], blk + 8u), from, to) : 0;
                     n += __builtin_amdgcn_update_dpp(0, n, 0xB1, 0xF, 0xF, false);  // the four lanes' sum
                     n += __builtin_amdgcn_update_dpp(0, n, 0x4E, 0xF, 0xF, false);
-                    a[u] += n;
+                    a[u] += (unsigned)n;
                     // all 32 places taken, and the list goes on
-                    more = more && a[u] == b0 + 32 && a[u] < end[u];
-                    if (more && a[u] + 8 * sub < end[u])
-                        v[u] = *reinterpret_cast<const uint4 *>(g.vs_win + a[u] + 8 * sub);
+                    more = more && a[u] == b0 + 32u && a[u] < end[u];
+                    if (more && a[u] + 8u * sub < end[u])
+                        v[u] = *reinterpret_cast<const uint4 *>(g.vs_win + a[u] + 8u * sub);
                 }
-                if (sub == 0 && m0 + u * groups < members) sm.cur[m0 + u * groups] = a[u];
+                if (sub == 0 && m0 + u * groups < members) sm.cur[m0 + u * groups] = (int)a[u];
             }
         }
     } else {  // more members than have cursors
@@ -417,9 +418,9 @@ __device__ __forceinline__ void hub_count_rest(HubSmem<ROWS> &sm, const Pruned &
             int r, a, end;
             hub_member(sm, g, min_degree, idx, ja + from, ja + to, r, a, end);
             while (a < end) {
-                const int blk = a & ~7;
-                const int n = hub_add_block(cnt, r * stride, *reinterpret_cast<const uint4 *>(g.vs_win + blk), blk, a,
-                                            min(end, blk + 8), from, to);
+                const unsigned blk = block_at((unsigned)a);
+                const int n = hub_add_block(cnt, r * stride, *reinterpret_cast<const uint4 *>(g.vs_win + blk), blk,
+                                            (unsigned)a, min((unsigned)end, blk + 8u), from, to);
                 if (n == 0) break;  // (a list that does not ascend)
                 a += n;
             }

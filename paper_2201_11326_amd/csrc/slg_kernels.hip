@@ -576,8 +576,8 @@ __global__ __launch_bounds__(256) void row_piece_kernel(Pruned g, int32_t *__res
 #pragma unroll
         for (int u = 0; u < kPlanAhead; ++u) {
             id[u] = (int)r;
-            p[u] = (int)a + 64 * u + lane;
-            in[u] = p[u] < b;
+            p[u] = (int)(a + 64 * u + lane);
+            in[u] = a + 64 * u + lane < b;  // in 64 bits: the rest of the piece may lie past 2^31
         }
         plan_members(g, id, p, in, tail_beg, tail_end, wu, ju, bu);
 #pragma unroll

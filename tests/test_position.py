@@ -1,4 +1,4 @@
-"""Search midpoints (csrc/slg_position.h) over the positions that lists of
+"""Search midpoints and aligned blocks (csrc/slg_position.h) over the positions that lists of
 fewer than 2^31 entries have, compiled and run on the host."""
 import shutil
 import subprocess
@@ -24,15 +24,23 @@ int main() {
                 return 1;
             }
         }
+    // a list's last position: its own block begins inside the list, the next ones past its end
+    for (int end : at) {
+        if (end < 1) continue;
+        const unsigned last = (unsigned)end - 1u, own = slg::block_at(last);
+        if (own > last || own + 7u < last || own % 8u) return 2;
+        for (unsigned ahead = 1; ahead < 8; ++ahead)
+            if (slg::block_at(last, ahead) != own + 8u * ahead || slg::block_at(last, ahead) <= last) return 3;
+    }
     return 0;
 }
 """
 
 
 @pytest.mark.skipif(not CXX, reason="no host C++ compiler")
-def test_middle(tmp_path):
+def test_middle_and_blocks(tmp_path):
     (tmp_path / "p.cpp").write_text(PROGRAM)
     subprocess.run([CXX, "-std=c++17", "-I", build.CSRC, str(tmp_path / "p.cpp"), "-o", str(tmp_path / "p")],
                    check=True)
     out = subprocess.run([str(tmp_path / "p")], capture_output=True, text=True)
-    assert out.returncode == 0, out.stdout
+    assert out.returncode == 0, (out.returncode, out.stdout)
