@@ -90,7 +90,7 @@ def probe_large() -> None:
         return False
 
     ctx.reset_timing()
-    ctx.line_graph_stream(g, [8, 16], 2 << 30, on_chunk, rows=(r0, r1))
+    ctx.line_graph_stream(g, [8, 16], 8 << 30, on_chunk, rows=(r0, r1))
     torch.cuda.synchronize()
     print(f"probe done: rows [{r0}, {r1}), {edges[0]} edges, work {ctx.work()}", flush=True)
 
